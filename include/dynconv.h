@@ -234,10 +234,10 @@ size_t dynconv_stack_workspace_bytes(dynconv_shape s, const dynconv_block *blks,
  * With DYNCONV_STACK_DENSE the mask units are skipped and every block runs on
  * all positions (the baseline of Eq. 1).
  *
- * Execution: when s.c <= 64 (fp32) or s.c <= 128 (fp16, bf16) and
- * DYNCONV_STACK_UNFUSED is not set, each
+ * Execution: when s.c <= 64 (fp32), or s.c <= 128, 160 or 192 (fp16, bf16),
+ * and DYNCONV_STACK_UNFUSED is not set, each
  * block is ONE kernel over small patches of the image (at most 256
- * positions, at most 32 columns wide), each of which builds the active and
+ * positions, at most 40 columns wide), each of which builds the active and
  * halo lists of its patch on chip (ballot ranks in raster order), gathers,
  * expands, runs the depthwise and the projection, adds the identity path and
  * computes the next block's mask (the first block also runs its own mask
@@ -332,7 +332,7 @@ dynconv_status dynconv_stack_forward_noalloc(const void *x, void *y, dynconv_sha
  * channels (the caller zero-pads PyTorch's cb-channel weights; since the
  * padded input channels are zero, their weight columns do not matter, and
  * outputs cb .. cp-1 are discarded).  c_hidden is a multiple of 16 (pad
- * with zero weights).  Execution: when cp fits the one-launch block kernel
+ * with zero weights).  Execution: when cp fits the one-launch unit
  * (cp <= 64 in fp32, cp <= 128 in fp16/bf16), cb * sizeof(dtype) is a
  * multiple of 4 and DYNCONV_STACK_UNFUSED is not set, each unit is ONE
  * launch on the unit's own rows: it stages the branch half (zero-extended

@@ -13,6 +13,7 @@
 #include "dynconv.h"
 #include "cells.h"
 #include "fused.h"
+#include "wide.h"
 #include "kernels.h"
 #include "shuffle.h"
 #include "dense.h"
@@ -282,8 +283,9 @@ void dispatch_mask(dynconv_dtype dt, const void *x, dynconv_shape s, const float
 }
 
 // ------------------------------------------------------------ fused block
-// Patches of the one-launch block kernel: the configuration PatchCfgOf picks
-// for the element type and channel bound.
+// Patches of k_block_fused: the configuration PatchCfgOf picks for the element
+// type and channel bound.  Their number is also the room for the per-patch
+// counts at the widths that only k_block_wide runs.
 template <typename T, int MAXC>
 PatchGeom fused_geom_t(dynconv_shape s) {
     typedef typename PatchCfgOf<T, MAXC>::type CFG;
@@ -336,29 +338,157 @@ void launch_fused_k(const void *src, void *dst, dynconv_shape s, const dynconv_b
            next ? fm.mask_next : nullptr, fm.band_counts, fm.mask_mode);
 }
 
+// Patches of the channel-parallel one-launch kernel: the cut into nph x npw
+// patches with the least estimated time.  A patch costs a fixed part (staging,
+// lists, the barriers and latencies of its chunks) plus its tiles of 16 needed
+// and own positions; patches beyond one per compute unit queue up.
+WideGeom wide_geom_of(dynconv_shape s, int64_t max_patches, int max_need) {
+    WideGeom best{};
+    double best_cost = 0.0;
+    const int w0 = (s.w + kWideMaxCols - 1) / kWideMaxCols;
+    int last_wu = 0;
+    for (int npw_t = w0; npw_t <= s.w && npw_t < w0 + 16; ++npw_t) {
+        const int wu = (s.w + npw_t - 1) / npw_t;
+        if (wu == last_wu) continue;
+        last_wu = wu;
+        const int npw = (s.w + wu - 1) / wu;
+        const int rmax = std::min({s.h, kWideOwn / wu, kWideSlots / (wu + 2) - 2});
+        if (rmax < 1) continue;
+        int last_r = 0;
+        const int h0 = (s.h + rmax - 1) / rmax;
+        for (int nph_t = h0; nph_t <= s.h && nph_t < h0 + 8; ++nph_t) {
+            const int r = (s.h + nph_t - 1) / nph_t;
+            if (r == last_r) continue;
+            last_r = r;
+            const int nph = (s.h + r - 1) / r;
+            const int64_t patches = static_cast<int64_t>(s.n) * nph * npw;
+            if (patches > max_patches) continue;
+            const int need = (r + std::min(nph - 1, 2)) * (wu + std::min(npw - 1, 2));
+            if (need > max_need) continue;
+            const double load = std::max(1.0, static_cast<double>(patches) / 256.0);
+            const double cost = load * (8 + (need + 15) / 16 + (r * wu + 15) / 16);
+            if (best.R == 0 || cost < best_cost - 1e-9) {
+                best_cost = cost;
+                best.R = r;
+                best.Wu = wu;
+                best.nph = nph;
+                best.npw = npw;
+            }
+        }
+    }
+    if (best.R == 0) return best;  // no cut within max_patches
+    best.slots = (best.R + 2) * (best.Wu + 2);
+    best.m_wp = div20_mul(best.Wu + 2);
+    best.m_wu = div20_mul(best.Wu);
+    return best;
+}
+
+// The x fragments of 8 needed tiles fit the registers up to 96 channels; above
+// that the patches are kept to 4 tiles (64 needed positions).  Where that
+// would take more than max_patches (97 to 128 channels, wide images), to 8.
+WideGeom wide_geom(dynconv_shape s, int64_t max_patches) {
+    WideGeom g = wide_geom_of(s, max_patches, s.c <= 96 ? 128 : 64);
+    if (g.R == 0) g = wide_geom_of(s, max_patches, 128);
+    const int need = (g.R + std::min(g.nph - 1, 2)) * (g.Wu + std::min(g.npw - 1, 2));
+    g.tiles = need <= 32 ? 2 : need <= 64 ? 4 : 8;
+    return g;
+}
+
+template <typename T, bool DENSE, int KS, int EC, int NT, bool ONE>
+void launch_wide_k(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
+                   const FusedMasks &fm, WideGeom g, hipStream_t st, Marks &mk) {
+    const int npatch = s.n * g.nph * g.npw;
+    const int grid = (npatch + 7) / 8 * 8;  // whole groups of 8 (one per XCD)
+    g.m_pieces = div20_mul(s.c / 8);
+    const size_t lds = wide_lds_bytes<T, EC, ONE>(s.c, g.slots);
+    auto go = [&](auto kern) {
+        launch(mk, kern, dim3(grid), dim3(kWideThreads), lds, st, static_cast<const T *>(src), static_cast<T *>(dst),
+               s.n, s.h, s.w, s.c, b->c_hidden, g, fm.shuffle_cb, fm.mask_in, fm.self ? b->w_mask : nullptr,
+               b->b_mask, fm.mask_self, static_cast<const T *>(b->w_expand), b->b_expand, b->act_expand,
+               static_cast<const T *>(b->w_dw), b->b_dw, b->act_dw, static_cast<const T *>(b->w_project),
+               b->b_project, b->act_project, next ? next->w_mask : nullptr, next ? next->b_mask : 0.0f,
+               next ? fm.mask_next : nullptr, reinterpret_cast<uint16_t *>(fm.band_counts), fm.mask_mode);
+    };
+    if constexpr (KS <= 4) {
+        if (fm.shuffle_cb) {
+            go(k_block_wide<T, DENSE, KS, true, EC, NT, ONE>);
+            return;
+        }
+    }
+    go(k_block_wide<T, DENSE, KS, false, EC, NT, ONE>);
+}
+
+// The instantiation for the channels, the hidden width and the patches' needed
+// tiles.  EC = 128 hidden channels per chunk halves the barriers and loads
+// each weight once per workgroup; 64 where the registers or (fp32) the LDS
+// don't hold 128, and where 64 are all there are.
+template <typename T, bool DENSE>
+void launch_wide(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
+                 const FusedMasks &fm, const WideGeom &g, hipStream_t st, Marks &mk) {
+#define DC_WIDE_K(KS, EC, NT, ONE) launch_wide_k<T, DENSE, KS, EC, NT, ONE>(src, dst, s, b, next, fm, g, st, mk)
+    if constexpr (sizeof(T) == 4) {  // at most 64 channels (use_fused)
+        if (s.c <= 32) {
+            if (g.tiles == 8) DC_WIDE_K(1, 64, 8, false);
+            else DC_WIDE_K(1, 64, 4, false);
+        } else {
+            if (g.tiles == 8) DC_WIDE_K(2, 64, 8, false);
+            else DC_WIDE_K(2, 64, 4, false);
+        }
+    } else if (s.c <= 32) {
+        DC_WIDE_K(1, 128, 8, false);
+    } else if (s.c <= 64) {
+        if (b->c_hidden <= 64) DC_WIDE_K(2, 64, 8, true);
+        else if (b->c_hidden <= 128) DC_WIDE_K(2, 128, 8, true);
+        else if (g.tiles == 8) DC_WIDE_K(2, 128, 8, false);
+        else DC_WIDE_K(2, 128, 4, false);
+    } else if (s.c <= 96) {
+        if (g.tiles == 8) DC_WIDE_K(3, 128, 8, false);
+        else DC_WIDE_K(3, 128, 4, false);
+    } else if (s.c <= 128) {
+        if (g.tiles == 8) DC_WIDE_K(4, 64, 8, false);
+        else if (b->c_hidden <= 128) DC_WIDE_K(4, 128, 4, true);
+        else DC_WIDE_K(4, 128, 4, false);
+    } else if (s.c <= 160) {
+        if (g.tiles == 2) DC_WIDE_K(5, 128, 2, false);
+        else DC_WIDE_K(5, 64, 4, false);
+    } else {
+        DC_WIDE_K(6, 64, 4, false);
+    }
+#undef DC_WIDE_K
+}
+
 template <typename T, bool DENSE>
 void launch_fused(const void *src, void *dst, dynconv_shape s, const dynconv_block *b,
                   const dynconv_block *next, const FusedMasks &fm, hipStream_t st, Marks &mk) {
     if (s.c <= 32)
         launch_fused_k<T, DENSE, 1, 2, 32>(src, dst, s, b, next, fm, st, mk);
-    else if (s.c <= 64)
+    else if constexpr (sizeof(T) == 2)  // up to 64 channels, 16-bit only (pick_wide)
         launch_fused_k<T, DENSE, 2, 4, 64>(src, dst, s, b, next, fm, st, mk);
-    else if constexpr (sizeof(T) == 2)  // 16-bit only (use_fused keeps fp32 at 64)
-        launch_fused_k<T, DENSE, 4, 8, 128>(src, dst, s, b, next, fm, st, mk);
 }
 
+// geom: the patches of the channel-parallel kernel, or none (R = 0): k_block_fused
 void dispatch_fused(dynconv_dtype dt, bool dense, const void *src, void *dst, dynconv_shape s,
-                    const dynconv_block *b, const dynconv_block *next, const FusedMasks &fm,
+                    const dynconv_block *b, const dynconv_block *next, const FusedMasks &fm, const WideGeom &geom,
                     hipStream_t st, Marks &mk) {
 #define DC_FUSED(T)                                                                  \
     (dense ? launch_fused<T, true>(src, dst, s, b, nullptr, dense_fm, st, mk)        \
            : launch_fused<T, false>(src, dst, s, b, next, fm, st, mk))
+#define DC_WIDE(T)                                                                   \
+    (dense ? launch_wide<T, true>(src, dst, s, b, nullptr, dense_fm, geom, st, mk)   \
+           : launch_wide<T, false>(src, dst, s, b, next, fm, geom, st, mk))
     FusedMasks dense_fm;
     dense_fm.shuffle_cb = fm.shuffle_cb;
+    if (geom.R != 0) {
+        if (dt == DYNCONV_F32) DC_WIDE(float);
+        else if (dt == DYNCONV_F16) DC_WIDE(half_t);
+        else DC_WIDE(bf16_t);
+        return;
+    }
     if (dt == DYNCONV_F32) DC_FUSED(float);
     else if (dt == DYNCONV_F16) DC_FUSED(half_t);
     else DC_FUSED(bf16_t);
 #undef DC_FUSED
+#undef DC_WIDE
 }
 
 // ------------------------------------------------------------ balanced cells
@@ -447,10 +577,14 @@ constexpr int32_t kStackFlags = kStackDense | kStackUnfused | kStackGSoftmax;
 
 int mask_mode_of(int32_t flags) { return (flags & kStackGSoftmax) ? 1 : 0; }
 
-// The one-launch block kernel covers up to 64 channels in fp32 and 128 in
-// fp16/bf16; wider blocks run the unfused kernel chain.
+// The one-launch block kernels cover up to 64 channels in fp32, and in
+// fp16/bf16 up to 128 and the whole 32-channel steps up to 192 (160 and 192;
+// MobileNetV2's 7x7x160 pair at batch 64: 151 us on the kernel chain, 48 on one
+// launch per block); wider blocks run the unfused kernel chain.
 bool use_fused(dynconv_shape s, dynconv_dtype dt, int32_t flags) {
-    return !(flags & kStackUnfused) && s.c <= (dt == DYNCONV_F32 ? kMaxFusedC : kMaxFusedC16);
+    if (flags & kStackUnfused) return false;
+    if (dt == DYNCONV_F32) return s.c <= kMaxFusedC;
+    return s.c <= kMaxFusedC16 || (s.c <= kMaxWideC && s.c % 32 == 0);
 }
 
 // Narrow 16-bit blocks (at most 32 channels, 192 hidden) run the
@@ -464,8 +598,34 @@ bool use_cells(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int
     return true;
 }
 
+// Which patch kernel a stack takes: the channel-parallel one (its patches), or
+// k_block_fused (R = 0), whose patches of 128 or 256 positions amortise their
+// fixed part better once a compute unit has many.  Measured per block, this
+// kernel against k_block_fused, fp16 unless noted:
+//   above 64 channels (only this one now; k_block_fused took up to 128):
+//     64 x 14x14x96: 17.5 / 42 us; 96 x 30x30x96: 71 / 190 us
+//   33 to 64 channels: 64 x 14x14x64, hidden 384 (256 patches): 12.3 / 24.8
+//     us; 96 x 28x28x64 (1,344 patches): 55 / 58, dense 67 / 61; 300 x 28x28x64
+//     (4,200 patches): 153 / 120 us; hidden widths of one chunk (ShuffleNetV2,
+//     bf16, 64 x 28x28, 896 patches): 18 / 25 us
+//   fp32, 64 channels: 16 x 48x48: 83 / 132 us
+//   up to 32 channels, fp32: 1 x 32x32x32 (128 patches): 11.2 / 17.1 us;
+//     16 x 48x48x32 (576 patches): 39 / 30 us
+WideGeom pick_wide(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int32_t n_blocks,
+                   int64_t max_patches) {
+    const WideGeom g = wide_geom(s, max_patches);
+    if (g.R == 0 || s.c > (dt == DYNCONV_F32 ? 32 : 64)) return g;
+    int emax = 0;
+    for (int32_t b = 0; b < n_blocks; ++b) emax = std::max(emax, blks[b].c_hidden);
+    const int64_t patches = static_cast<int64_t>(s.n) * g.nph * g.npw;
+    const int64_t most = s.c <= 32 ? 256 : emax <= 128 ? INT64_MAX : 1024;
+    return patches <= most ? g : WideGeom{};
+}
+
 struct StackLayout {
     bool fused, cells;
+    WideGeom geom;  // patches of the channel-parallel kernel
+    int nbands;     // patches per block (per-patch counts)
     size_t masks, mask2, tbuf, active, dilated, nbr, counts, bands, scratch, hidden, cc0, cc1, total;
 };
 
@@ -492,7 +652,19 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
         L.masks = off;  off += align_up(npos);
         L.mask2 = off;  off += align_up(npos);
         L.counts = off; off += align_up(8 * static_cast<size_t>(n_blocks));
-        L.bands = off;  off += align_up(8 * static_cast<size_t>(n_blocks) * fused_patch_count(s, dt));
+        L.bands = off;
+        if (s.c <= kMaxFusedC16) {
+            // per-patch counts: 8 bytes a patch of k_block_fused; the
+            // channel-parallel kernel packs 2 bytes into the same room
+            L.nbands = fused_patch_count(s, dt);
+            off += align_up(8 * static_cast<size_t>(n_blocks) * L.nbands);
+            L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
+            if (L.geom.R != 0) L.nbands = s.n * L.geom.nph * L.geom.npw;
+        } else {
+            L.geom = wide_geom(s, INT64_MAX);
+            L.nbands = s.n * L.geom.nph * L.geom.npw;
+            off += align_up(2 * static_cast<size_t>(n_blocks) * L.nbands);
+        }
     } else {
         int emax = 0;
         for (int32_t b = 0; b < n_blocks; ++b)
@@ -538,6 +710,22 @@ struct Plan {
         return exec;
     }
 };
+
+// Per-patch counts of block b, and their reduction.
+int32_t *band_counts_of(const char *base, const StackLayout &L, int32_t b) {
+    const size_t per = L.geom.R != 0 ? 2 : 8;
+    return at<int32_t>(base, L.bands + per * static_cast<size_t>(L.nbands) * b);
+}
+
+void launch_band_counts(const char *base, const StackLayout &L, int32_t n_blocks, int32_t *counts, hipStream_t st,
+                        Marks &mk) {
+    if (L.geom.R != 0)
+        launch(mk, k_wide_counts, dim3(n_blocks), dim3(kBlock), 0, st, at<const uint16_t>(base, L.bands), L.nbands,
+               counts);
+    else
+        launch(mk, k_band_counts, dim3(n_blocks), dim3(kBlock), 0, st, at<const int32_t>(base, L.bands), L.nbands,
+               counts);
+}
 
 void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks,
                 int32_t n_blocks, int32_t flags, uint8_t *masks, int32_t *counts, char *base,
@@ -596,8 +784,6 @@ void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const
             if (masks) return masks + static_cast<size_t>(b) * npos;
             return at<uint8_t>(base, ((b % 2) ? L.mask2 : L.masks));
         };
-        const int nbands = fused_patch_count(s, dt);
-        int32_t *band_counts = at<int32_t>(base, L.bands);
         for (int32_t b = 0; b < n_blocks; ++b) {
             void *dst = ((n_blocks - 1 - b) % 2 == 0) ? y : tb;
             const dynconv_block *next = (b + 1 < n_blocks) ? &blks[b + 1] : nullptr;
@@ -607,14 +793,14 @@ void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const
             fm.mask_in = (b == 0) ? nullptr : mask_of(b);
             fm.mask_self = mask_of(0);
             fm.mask_next = next ? mask_of(b + 1) : nullptr;
-            fm.band_counts = band_counts + static_cast<size_t>(2) * nbands * b;
-            if (plan.note("k_block_fused")) dispatch_fused(dt, dense, src, dst, s, &blks[b], next, fm, st, mk);
+            fm.band_counts = band_counts_of(base, L, b);
+            if (plan.note("k_block_fused"))
+                dispatch_fused(dt, dense, src, dst, s, &blks[b], next, fm, L.geom, st, mk);
             src = dst;
         }
         // P, P_d per block only on request (listed in every plan)
         if (!dense && (counts || (!plan.exec && plan.list_counts)) && plan.note("k_band_counts"))
-            launch(mk, k_band_counts, dim3(n_blocks), dim3(kBlock), 0, st,
-                   static_cast<const int32_t *>(band_counts), nbands, cnt_all);
+            launch_band_counts(base, L, n_blocks, cnt_all, st, mk);
         return;
     }
     // Unfused chain, in place on y.
@@ -669,7 +855,7 @@ struct ShuffleLayout {
 bool shuffle_direct(dynconv_shape s, const dynconv_block *br, dynconv_dtype dt, int32_t flags) {
     dynconv_shape bs = s;
     bs.c = br[0].c_in;
-    return use_fused(bs, dt, flags) && (s.c / 2) * dtype_size(dt) % 4 == 0;
+    return use_fused(bs, dt, flags) && bs.c <= kMaxFusedC16 && (s.c / 2) * dtype_size(dt) % 4 == 0;
 }
 
 dynconv_shape branch_shape(dynconv_shape s, const dynconv_block *br) {
@@ -764,8 +950,6 @@ void shuffle_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, con
     // goes to bufs[1]); bufs[u % 2] for the kernel chain, which runs in place
     auto in_of = [&](int32_t u) -> void * { return L.fused ? bufs[0] : bufs[u % 2]; };
 
-    const int nbands = L.fused ? fused_patch_count(bs, dt) : 0;
-    int32_t *band_counts = at<int32_t>(ib, L.bands);
     if (SL.direct) {
         for (int32_t u = 0; u < n_units; ++u) {
             FusedMasks fm;
@@ -774,14 +958,14 @@ void shuffle_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, con
             if (!dense) {
                 fm.self = true;  // the unit's mask unit on the staged branch half
                 fm.mask_self = masks ? mask_of(u) : nullptr;
-                fm.band_counts = band_counts + static_cast<size_t>(2) * nbands * u;
+                fm.band_counts = band_counts_of(ib, L, u);
             }
             const void *xu = (u == 0) ? x : out_of(u - 1);
-            if (plan.note("k_block_fused")) dispatch_fused(dt, dense, xu, out_of(u), bs, &br[u], nullptr, fm, st, mk);
+            if (plan.note("k_block_fused"))
+                dispatch_fused(dt, dense, xu, out_of(u), bs, &br[u], nullptr, fm, L.geom, st, mk);
         }
         if (!dense && (counts || (!plan.exec && plan.list_counts)) && plan.note("k_band_counts"))
-            launch(mk, k_band_counts, dim3(n_units), dim3(kBlock), 0, st,
-                   static_cast<const int32_t *>(band_counts), nbands, cnt_all);
+            launch_band_counts(ib, L, n_units, cnt_all, st, mk);
         return;
     }
     if (plan.note("k_shuffle_split")) dispatch_split(dt, x, in_of(0), npos, cb, cp, st, mk);
@@ -800,11 +984,11 @@ void shuffle_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, con
             if (!dense) {
                 fm.self = true;  // the unit's mask unit on the staged branch input
                 fm.mask_self = masks ? mask_of(u) : nullptr;
-                fm.band_counts = band_counts + static_cast<size_t>(2) * nbands * u;
+                fm.band_counts = band_counts_of(ib, L, u);
             }
             bout = bufs[1];
             if (plan.note("k_block_fused"))
-                dispatch_fused(dt, dense, bin, bufs[1], bs, &br[u], nullptr, fm, st, mk);
+                dispatch_fused(dt, dense, bin, bufs[1], bs, &br[u], nullptr, fm, L.geom, st, mk);
         } else if (dense) {
             bool run = plan.note("k_expand");
             plan.note("k_dw_project");
@@ -828,8 +1012,7 @@ void shuffle_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, con
         if (plan.note("k_shuffle_merge")) dispatch_merge(dt, xu, bout, out_of(u), next_in, npos, cb, cp, st, mk);
     }
     if (L.fused && !dense && (counts || (!plan.exec && plan.list_counts)) && plan.note("k_band_counts"))
-        launch(mk, k_band_counts, dim3(n_units), dim3(kBlock), 0, st,
-               static_cast<const int32_t *>(band_counts), nbands, cnt_all);
+        launch_band_counts(ib, L, n_units, cnt_all, st, mk);
 }
 
 // ------------------------------------------------------------ whole networks

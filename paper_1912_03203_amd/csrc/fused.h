@@ -63,8 +63,8 @@ struct PatchCfg {
 //   16-bit, C <= 32: 8 x 32 patches, 8 waves, two workgroups per CU
 //   16-bit, C <= 64: 4 x 32 patches, 4 waves, two workgroups per CU
 //   fp32,   C <= 32: 8 x 32 patches, 8 waves, one workgroup per CU
-//   fp32,   C <= 64: 4 x 32 patches, 4 waves, one workgroup per CU
-//   16-bit, C <= 128: 64-position patches, 4 waves, two workgroups per CU
+// (fp32 up to 64 and 16-bit up to 128 channels: only the number of patches,
+// the blocks run k_block_wide)
 template <typename T, int MAXC> struct PatchCfgOf;
 template <int MAXC> struct PatchCfgOf<float, MAXC> {
     typedef typename std::conditional<MAXC <= 32, PatchCfg<256, 340, 8, 2>, PatchCfg<128, 208, 4, 1>>::type type;

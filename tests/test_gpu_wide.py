@@ -1,0 +1,94 @@
+"""The channel-parallel one-launch block kernel against the kernel chain, byte
+for byte, where its tiling changes: chunks of 64 or 128 hidden channels (one,
+several, a partial last one), 2, 4 or 8 tiles of needed positions, contraction
+tails, single rows, columns and positions, empty and full masks."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1912_03203_amd import dynconv as dc
+from paper_1912_03203_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _lib():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dc.load()
+
+
+CASES = [
+    # dtype, (N, H, W, C, E), density, blocks
+    ("f16", (1, 1, 1, 40, 16), 1.0, 1),          # one position, one chunk
+    ("bf16", (2, 9, 41, 64, 64), 0.4, 2),        # a chunk of 64, strips of less than 40 columns
+    ("f16", (2, 9, 13, 64, 80), 0.4, 2),         # one partial chunk of 128
+    ("f16", (3, 14, 14, 64, 384), 0.3, 2),       # three chunks
+    ("bf16", (300, 14, 14, 64, 208), 0.3, 1),    # 1,200 patches: k_block_fused
+    ("f16", (2, 11, 7, 72, 16), 0.5, 2),         # several-chunk form with one chunk, contraction tail
+    ("bf16", (3, 30, 29, 96, 144), 0.3, 2),      # 8 needed tiles, last chunk of 16
+    ("f16", (2, 8, 8, 96, 128), 0.0, 2),         # no active position
+    ("f16", (1, 6, 5, 104, 256), 1.0, 1),        # all active
+    ("bf16", (2, 33, 40, 128, 272), 0.4, 1),     # wide image
+    ("f16", (1, 3, 1000, 112, 144), 0.3, 1),     # 97-128 channels, 8 needed tiles
+    ("f16", (5, 7, 7, 160, 960), 0.4, 2),        # 2 needed tiles
+    ("bf16", (2, 16, 15, 160, 304), 0.4, 2),     # 4 needed tiles, chunks of 64
+    ("f16", (1, 9, 1, 192, 80), 0.5, 1),
+    ("f16", (2, 5, 6, 32, 208), 0.4, 2),         # above the cell kernel's hidden width
+    ("f32", (1, 7, 3, 8, 16), 0.5, 2),
+    ("f32", (2, 16, 17, 32, 192), 0.4, 2),
+    ("f32", (3, 12, 9, 64, 80), 0.4, 1),
+    ("f32", (90, 32, 32, 16, 32), 0.4, 1),       # more than 256 patches: k_block_fused
+]
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_%s" % (c[0], "x".join(map(str, c[1]))))
+def test_stack_equals_the_kernel_chain(case, dense):
+    dtype, (N, H, W, C, E), density, nb = case
+    rng = inputs.rng_for(N * H * W + C + E)
+    dt = dc.NAME_TO_DTYPE[dtype]
+    x = torch.from_numpy(inputs.blob_features(rng, N, H, W, C)).cuda().to(dt)
+    blocks = [dc.BlockWeights.from_arrays(inputs.block_weights(rng, C, E, dtype=dtype), dt) for _ in range(nb)]
+    logits = torch.empty(N * H * W, device="cuda")
+    dc.mask(x, blocks[0].w_mask, 0.0, logits=logits)
+    for b in blocks:  # about the density in the first block; extremes in all
+        b.b_mask = float("inf") if density == 1.0 else float("-inf") if density == 0.0 else float(
+            inputs.percentile_bias(logits.cpu().numpy(), density))
+    got = []
+    for flags in (0, dc.STACK_UNFUSED):
+        y = torch.full_like(x, float("nan"))
+        masks = torch.full((nb, N * H * W), 9, dtype=torch.uint8, device="cuda")
+        counts = torch.full((nb, 2), -1, dtype=torch.int32, device="cuda")
+        dc.stack_forward(x, y, blocks, flags | (dc.STACK_DENSE if dense else 0), None if dense else masks,
+                         None if dense else counts)
+        torch.cuda.synchronize()
+        got.append([t.cpu().view(torch.uint8).numpy() for t in (y, masks, counts)])
+    for a, b, what in zip(got[0], got[1], ("output", "masks", "counts")):
+        assert np.array_equal(a, b), what
+    # the same, in place
+    y = x.clone()
+    dc.stack_forward(y, y, blocks, dc.STACK_DENSE if dense else 0)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().view(torch.uint8).numpy(), got[0][0])
+
+
+@pytest.mark.parametrize("dtype,c,cp,e", [("bf16", 20, 16, 32), ("f16", 116, 64, 144), ("f32", 34, 24, 32),
+                                          ("bf16", 232, 120, 256), ("f16", 312, 160, 160)])
+def test_shuffle_units_equal_the_kernel_chain(dtype, c, cp, e):
+    rng = inputs.rng_for(c)
+    dt = dc.NAME_TO_DTYPE[dtype]
+    x = torch.from_numpy(inputs.blob_features(rng, 3, 9, 11, c)).cuda().to(dt)
+    br = [dc.BlockWeights.from_arrays(inputs.block_weights(rng, cp, e, dtype=dtype), dt, acts=(1, 0, 1))
+          for _ in range(3)]
+    got = []
+    for flags in (0, dc.STACK_UNFUSED):
+        y = torch.full_like(x, float("nan"))
+        masks = torch.full((3, 3 * 9 * 11), 9, dtype=torch.uint8, device="cuda")
+        counts = torch.full((3, 2), -1, dtype=torch.int32, device="cuda")
+        dc.ShuffleStack(x, y, br, flags, masks, counts)()
+        torch.cuda.synchronize()
+        got.append([t.cpu().view(torch.uint8).numpy() for t in (y, masks, counts)])
+    for a, b, what in zip(got[0], got[1], ("output", "masks", "counts")):
+        assert np.array_equal(a, b), what
