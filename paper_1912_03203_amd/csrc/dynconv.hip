@@ -720,11 +720,11 @@ int32_t *band_counts_of(const char *base, const StackLayout &L, int32_t b) {
 void launch_band_counts(const char *base, const StackLayout &L, int32_t n_blocks, int32_t *counts, hipStream_t st,
                         Marks &mk) {
     if (L.geom.R != 0)
-        launch(mk, k_wide_counts, dim3(n_blocks), dim3(kBlock), 0, st, at<const uint16_t>(base, L.bands), L.nbands,
-               counts);
+        launch(mk, k_band_counts<uint16_t>, dim3(n_blocks), dim3(kCountThreads), 0, st,
+               at<const uint16_t>(base, L.bands), L.nbands, counts);
     else
-        launch(mk, k_band_counts, dim3(n_blocks), dim3(kBlock), 0, st, at<const int32_t>(base, L.bands), L.nbands,
-               counts);
+        launch(mk, k_band_counts<int2>, dim3(n_blocks), dim3(kCountThreads), 0, st, at<const int2>(base, L.bands),
+               L.nbands, counts);
 }
 
 void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks,
@@ -768,8 +768,8 @@ void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const
             src = dst;
         }
         if (!dense && (counts || (!plan.exec && plan.list_counts)) && plan.note("k_band_counts"))
-            launch(mk, k_band_counts, dim3(n_blocks), dim3(kBlock), 0, st,
-                   static_cast<const int32_t *>(band_counts), static_cast<int>(ncells), cnt_all);
+            launch(mk, k_band_counts<int2>, dim3(n_blocks), dim3(kCountThreads), 0, st, at<const int2>(base, L.bands),
+                   static_cast<int>(ncells), cnt_all);
         return;
     }
     if (L.fused) {

@@ -640,31 +640,56 @@ k_block_fused(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
     }
 }
 
-// counts[2b], counts[2b+1] = sums of the per-patch counts of block b
-// (one workgroup per block, fixed summation order).
-__global__ void __launch_bounds__(kBlock)
-k_band_counts(const int32_t *__restrict__ band_counts, int nbands, int32_t *__restrict__ counts) {
-    __shared__ int2 part[kBlock];
-    const int b = blockIdx.x;
-    const int2 *src = reinterpret_cast<const int2 *>(band_counts) + static_cast<int64_t>(b) * nbands;
-    int2 acc = make_int2(0, 0);
-    for (int i = threadIdx.x; i < nbands; i += kBlock) {
-        const int2 v = src[i];
-        acc.x += v.x;
-        acc.y += v.y;
-    }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
-        if (static_cast<int>(threadIdx.x) < off) {
-            part[threadIdx.x].x += part[threadIdx.x + off].x;
-            part[threadIdx.x].y += part[threadIdx.x + off].y;
+// counts[2b], counts[2b+1] = sums of the per-patch (per-cell) counts of block b:
+// int2 pairs, or both counts in the bytes of a uint16 (k_block_wide).  One
+// workgroup per block; every thread has 8 loads in flight, because the time is
+// the loads' latency (6,272 cells of a 32 x 56x56 block: 7.0 us with 256 threads
+// and one load at a time, 2.9 so).
+constexpr int kCountThreads = 1024;
+template <typename P>
+__global__ void __launch_bounds__(kCountThreads)
+k_band_counts(const P *__restrict__ band_counts, int nbands, int32_t *__restrict__ counts) {
+    __shared__ int2 part[kCountThreads / kWave];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const P *src = band_counts + static_cast<int64_t>(b) * nbands;
+    int a = 0, d = 0;
+    auto add = [&](P v) {
+        if constexpr (sizeof(P) == 8) {
+            a += v.x;
+            d += v.y;
+        } else {
+            a += v & 0xff;
+            d += v >> 8;
         }
-        __syncthreads();
+    };
+    int i = tid;
+    for (; i + 7 * kCountThreads < nbands; i += 8 * kCountThreads) {
+        P v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = src[i + q * kCountThreads];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) add(v[q]);
     }
-    if (threadIdx.x == 0) {
-        counts[2 * b] = part[0].x;
-        counts[2 * b + 1] = part[0].y;
+    P v[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] = (i + q * kCountThreads < nbands) ? src[i + q * kCountThreads] : P{};
+#pragma unroll
+    for (int q = 0; q < 7; ++q) add(v[q]);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        a += __shfl_down(a, off);
+        d += __shfl_down(d, off);
+    }
+    if (tid % kWave == 0) part[tid / kWave] = make_int2(a, d);
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < kCountThreads / kWave; ++w) {
+            a += part[w].x;
+            d += part[w].y;
+        }
+        counts[2 * b] = a;
+        counts[2 * b + 1] = d;
     }
 }
 

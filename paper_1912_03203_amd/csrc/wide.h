@@ -671,31 +671,4 @@ k_block_wide(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int 
             mask_of_row<T, KS>(xs + tid * XP, C, wm_next, bm_next, mask_mode) ? 1 : 0;
 }
 
-// counts[2b], counts[2b+1] = sums of the per-patch counts of block b.
-__global__ void __launch_bounds__(kBlock)
-k_wide_counts(const uint16_t *__restrict__ band_counts, int nbands, int32_t *__restrict__ counts) {
-    __shared__ int2 part[kBlock];
-    const int b = blockIdx.x;
-    const uint16_t *src = band_counts + static_cast<int64_t>(b) * nbands;
-    int2 acc = make_int2(0, 0);
-    for (int i = threadIdx.x; i < nbands; i += kBlock) {
-        const int v = src[i];
-        acc.x += v & 0xff;
-        acc.y += v >> 8;
-    }
-    part[threadIdx.x] = acc;
-    __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
-        if (static_cast<int>(threadIdx.x) < off) {
-            part[threadIdx.x].x += part[threadIdx.x + off].x;
-            part[threadIdx.x].y += part[threadIdx.x + off].y;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        counts[2 * b] = part[0].x;
-        counts[2 * b + 1] = part[0].y;
-    }
-}
-
 }  // namespace dynconv
