@@ -39,7 +39,10 @@ __host__ __device__ constexpr size_t pw_lds_bytes() {
     return static_cast<size_t>(OT) * 16 * (KB * 32 + 8) * sizeof(T);
 }
 
-template <typename T, int OT, int KB>
+// MULTI: more than one chunk; the next chunk's weights and x are in flight
+// while the current one is contracted (their registers would cost the one-chunk
+// form a third of its waves: 14x14, batch 64, 96 -> 576 15.0 -> 18.2 us).
+template <typename T, int OT, int KB, bool MULTI>
 __global__ void __launch_bounds__(kBlock)
 k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, const float *__restrict__ b,
           int O, int act, const T *__restrict__ res, T *__restrict__ y, int nor) {
@@ -113,7 +116,7 @@ k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, co
     };
     const int64_t step = nslot * 8;
     const int64_t lane_p = wave * 16 + r;  // this lane's position within a tile (B column)
-    if (nch == 1) {
+    if constexpr (!MULTI) {
         // weights staged once; the next tile's x is requested before the
         // current tile is contracted
         stage(0);
@@ -135,22 +138,121 @@ k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, co
             contract(acc, bx);
             finish(acc, pt * kPwPos + lane_p);
         }
-        return;
-    }
-    for (int64_t pt = slot * 8 + xcd; pt < ptiles; pt += step) {
-        const int64_t p = pt * kPwPos + lane_p;
-        floatx4 acc[OT];
-        init(acc);
-        for (int ch = 0; ch < nch; ++ch) {
-            const int c_base = ch * KB * 32;
-            Frag bx[KB];
-            load_x(bx, p, c_base);
-            __syncthreads();  // every wave is done with the previous chunk
-            stage(c_base);
-            __syncthreads();
-            contract(acc, bx);
+    } else {
+        constexpr int WP = (ROWS * PIECES + kBlock - 1) / kBlock;
+        Frag wv[WP], bn[KB];
+        auto load_w = [&](int c_base) {
+#pragma unroll
+            for (int q = 0; q < WP; ++q) {
+                const int i = threadIdx.x + q * kBlock;
+                const int row = i / PIECES, c = c_base + (i % PIECES) * 8;
+                const int o = o_base + row;
+                const bool in = i < ROWS * PIECES && o < O && c < C;
+                wv[q] = M::load(w + (in ? static_cast<int64_t>(o) * C + c : 0));
+                if (!in) wv[q] = M::zero();
+            }
+        };
+        auto store_w = [&]() {
+#pragma unroll
+            for (int q = 0; q < WP; ++q) {
+                const int i = threadIdx.x + q * kBlock;
+                if (i < ROWS * PIECES) *reinterpret_cast<Frag *>(ws + (i / PIECES) * LD + (i % PIECES) * 8) = wv[q];
+            }
+        };
+        for (int64_t pt = slot * 8 + xcd; pt < ptiles; pt += step) {
+            const int64_t p = pt * kPwPos + lane_p;
+            load_w(0);
+            load_x(bn, p, 0);
+            floatx4 acc[OT];
+            init(acc);
+            for (int ch = 0; ch < nch; ++ch) {
+                Frag bx[KB];
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) bx[kb] = bn[kb];
+                __syncthreads();  // every wave is done with the previous chunk
+                store_w();
+                __syncthreads();
+                if (ch + 1 < nch) {
+                    load_w((ch + 1) * KB * 32);
+                    load_x(bn, p, (ch + 1) * KB * 32);
+                }
+                contract(acc, bx);
+            }
+            finish(acc, p);
         }
-        finish(acc, p);
+    }
+}
+
+// ---------------------------------------------- pointwise, few positions
+// The same contraction where a tile of 16 outputs x 16 positions per wave is all
+// there is (single images): every wave on its own, both operands straight from
+// the caches into a ring of D steps of 32 channels, without LDS, barriers or
+// branches around the loads (what is in flight is known at every wait).
+// Accumulation as in k_conv1x1 (bias first, steps of 32 channels ascending), so
+// the outputs are the same.  Bound by the latency of the first loads; k_conv1x1
+// pays two barriers and a memory latency per 256 channels there.  At 7x7, one
+// image: 960 -> 320 12.1 -> 9.0 us, 320 -> 1280 7.8 -> 4.4, 576 -> 160 9.2 -> 6.1.
+// The four waves of a workgroup take neighbouring output tiles of the same
+// positions.
+template <typename T, int D>
+__global__ void __launch_bounds__(kBlock)
+k_conv1x1_tile(const T *__restrict__ x, int P, int C, const T *__restrict__ w, const float *__restrict__ b, int O,
+               int act, const T *__restrict__ res, T *__restrict__ y, int nog) {
+    typedef mma<T> M;
+    typedef typename M::frag Frag;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), lane = threadIdx.x % kWave;
+    const int r = lane % 16, g = lane / 16;
+    const int og = blockIdx.x % nog, p0 = (blockIdx.x / nog) * 16;
+    const int o0 = (og * kWavesPerBlock + wave) * 16;
+    if (o0 >= O) return;  // uniform per wave, no barrier below
+    const int nks = (C + 31) / 32;
+    // rows past P or O read the last one; their products are not stored
+    const T *xr = x + static_cast<int64_t>(min(p0 + r, P - 1)) * C;
+    const T *wr = w + static_cast<int64_t>(min(o0 + r, O - 1)) * C;
+    Frag a[D], v[D];
+    auto load = [&](int ks, int d) {
+        const int c = min(ks * 32 + 8 * g, C - 8);  // past C: zeroed before use
+        a[d] = M::load(wr + c);
+        v[d] = M::load(xr + c);
+    };
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) load(d, d);
+    const int o = o0 + 4 * g;
+    floatx4 acc;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = b[min(o + q, O - 1)];
+    auto step = [&](int ks, int d) {
+        if (ks * 32 + 8 * g >= C) {  // the contraction's tail
+            a[d] = M::zero();
+            v[d] = M::zero();
+        }
+        acc = M::run(a[d], v[d], acc);
+    };
+    int ks = 0;
+    for (; ks + D <= nks; ks += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            load(ks + d + D - 1, (d + D - 1) % D);
+            step(ks + d, d);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d)
+        if (ks + d < nks) step(ks + d, d);
+    const float lo = act_lo(act), hi = act_hi(act);
+    const int p = p0 + r;
+    if (p < P && o < O) {  // O is a multiple of 8: all four outputs exist
+        const int64_t at = static_cast<int64_t>(p) * O + o;
+        float out[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q] = clamp_act(acc[q], lo, hi);
+        if (res) {
+            float rv[4];
+            io<T>::load4(res + at, rv);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) out[q] += rv[q];
+        }
+        io<T>::store4(y + at, out);
     }
 }
 
@@ -160,39 +262,59 @@ k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, co
 // rows of its R output rows once: each input row's three taps (16-byte
 // loads, zeros past the left and right edges) feed every output row that
 // uses it, so a lane issues (S (R - 1) + 3) x 3 tap loads for R outputs
-// instead of 9 R.  The 9 weight vectors are loaded once per task.  Each
-// output accumulates in fp32 from the bias, taps in (kh, kw) order; rows
-// outside the image are skipped.
+// instead of 9 R.  The 72 weights of the lane's 8 channels are contiguous in
+// memory ([C][9]): each lane reads them itself, with the taps of the first
+// rows in flight behind them.  Each output accumulates in fp32 from the bias,
+// taps in (kh, kw) order; rows outside the image are skipped.
+// Bound by the latency of these loads: few work items take small R, so that
+// more waves are in flight (launch_dwconv_s).  All weights staged per
+// workgroup through LDS (9 C two-byte loads and a division each, and a barrier)
+// took 8.2 us for 14x14x576 -> 7x7 of one image, now 4.1; at batch 64 9.6, now
+// 7.0.
+template <typename T>
+struct DwWeights {  // [8][9]
+    struct __attribute__((packed, aligned(2))) raw_t {
+        uint32_t v[36];
+    };
+    raw_t w;
+    __device__ __forceinline__ void load(const T *p) { w = *reinterpret_cast<const raw_t *>(p); }
+    __device__ __forceinline__ float at(int u, int k) const {
+        const int i = u * 9 + k;
+        typedef T pair_t __attribute__((ext_vector_type(2)));
+        return static_cast<float>(__builtin_bit_cast(pair_t, w.v[i / 2])[i % 2]);
+    }
+};
+template <>
+struct DwWeights<float> {
+    float w[72];
+    __device__ __forceinline__ void load(const float *p) {
+#pragma unroll
+        for (int i = 0; i < 72; ++i) w[i] = p[i];
+    }
+    __device__ __forceinline__ float at(int u, int k) const { return w[u * 9 + k]; }
+};
+
 template <typename T, int S, int R>
 __global__ void __launch_bounds__(kBlock)
 k_dwconv3x3(const T *__restrict__ x, int N, int H, int W, int C, const T *__restrict__ w,
             const float *__restrict__ b, int act, T *__restrict__ y, int Ho, int Wo) {
     typedef typename io<T>::vec8 V;
     constexpr int ROWS = S * (R - 1) + 3;  // input rows of R output rows
-    extern __shared__ __align__(16) unsigned char dw_smem[];
-    T *wt = reinterpret_cast<T *>(dw_smem);  // [9][C]: the taps, transposed
-    for (int i = threadIdx.x; i < 9 * C; i += kBlock) {
-        const int ch = i / 9, k = i % 9;
-        wt[k * C + ch] = w[i];
-    }
-    __syncthreads();
     const float lo = act_lo(act), hi = act_hi(act);
-    const int cgs = C / 8;
-    const int tasks = Wo * cgs;
-    const int chunks = (tasks + kBlock - 1) / kBlock;
-    const int rbs = (Ho + R - 1) / R;
-    const int64_t items = static_cast<int64_t>(N) * rbs * chunks;
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int chunk = static_cast<int>(it % chunks);
-        const int64_t nr = it / chunks;
-        const int rb = static_cast<int>(nr % rbs), n = static_cast<int>(nr / rbs);
-        const int task = chunk * kBlock + static_cast<int>(threadIdx.x);
+    const uint32_t cgs = C / 8;
+    const uint32_t tasks = Wo * cgs;
+    const uint32_t chunks = (tasks + kBlock - 1) / kBlock;
+    const uint32_t rbs = (Ho + R - 1) / R;
+    const uint32_t items = N * rbs * chunks;  // fits: fewer than the outputs' 8-channel groups
+    for (uint32_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const uint32_t nr = it / chunks, chunk = it - nr * chunks;
+        const uint32_t n = nr / rbs;
+        const int i0 = (nr - n * rbs) * R;  // first output row
+        const uint32_t task = chunk * kBlock + threadIdx.x;
         if (task >= tasks) continue;
-        const int cg = task % cgs, j = task / cgs, c = cg * 8;
-        const int i0 = rb * R;  // first output row
-        V wk[9];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) wk[k] = io<T>::raw8(wt + k * C + c);
+        const int j = task / cgs, c = (task - j * cgs) * 8;
+        DwWeights<T> wk;
+        wk.load(w + c * 9);
         float acc[R][8];
 #pragma unroll
         for (int q = 0; q < R; ++q)
@@ -221,8 +343,7 @@ k_dwconv3x3(const T *__restrict__ x, int N, int H, int W, int C, const T *__rest
                 for (int dw = 0; dw < 3; ++dw)
 #pragma unroll
                     for (int u = 0; u < 8; ++u)
-                        acc[q][u] = __builtin_fmaf(static_cast<float>(wk[dh * 3 + dw][u]),
-                                                   static_cast<float>(v[dw][u]), acc[q][u]);
+                        acc[q][u] = __builtin_fmaf(wk.at(u, dh * 3 + dw), static_cast<float>(v[dw][u]), acc[q][u]);
             }
         }
 #pragma unroll

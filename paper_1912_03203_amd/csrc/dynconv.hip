@@ -1181,15 +1181,21 @@ void launch_conv1x1_k(const void *x, int64_t P, int C, const void *w, const floa
     // one contraction chunk: as many workgroups as the device holds at once
     // (queried once), each staging the weights once and walking several
     // tiles; else one tile per workgroup
+    // smaller chunks hold the whole contraction (launch_conv1x1_ot)
+    constexpr bool kMulti = KB >= (sizeof(T) == 4 ? 2 : 4);
     const bool one_chunk = C <= KB * 32;
     static std::atomic<int64_t> resident{0};
     if (one_chunk && resident.load() == 0)
-        resident.store(resident_groups(k_conv1x1<T, OT, KB>, pw_lds_bytes<T, OT, KB>()));
+        resident.store(resident_groups(k_conv1x1<T, OT, KB, false>, pw_lds_bytes<T, OT, KB>()));
     const int64_t full = resident.load() > 0 ? resident.load() : 1024;
     const int64_t cap = one_chunk ? (full / 8 + nor - 1) / nor : 2048 / nor + 1;
     if (slots > cap) slots = cap;
     if (slots < 1) slots = 1;
-    launch(mk, k_conv1x1<T, OT, KB>, dim3(static_cast<unsigned>(slots * 8 * nor)), dim3(kBlock),
+    auto kern = k_conv1x1<T, OT, KB, false>;
+    if constexpr (kMulti) {
+        if (!one_chunk) kern = k_conv1x1<T, OT, KB, true>;
+    }
+    launch(mk, kern, dim3(static_cast<unsigned>(slots * 8 * nor)), dim3(kBlock),
            pw_lds_bytes<T, OT, KB>(), st, static_cast<const T *>(x), P, C, static_cast<const T *>(w), b, O, act,
            static_cast<const T *>(res), static_cast<T *>(y), nor);
 }
@@ -1213,9 +1219,27 @@ void launch_conv1x1_ot(const void *x, int64_t P, int C, const void *w, const flo
     else if constexpr (kFits8) launch_conv1x1_k<T, OT, 8>(x, P, C, w, b, O, act, res, y, st, mk);
 }
 
+// One tile of 16 outputs x 16 positions per wave (k_conv1x1_tile) up to 1,024
+// tiles, a wave per SIMD (above, k_conv1x1's sharing of weights and x wins: 7x7,
+// batch 64, 576 -> 160, 1,960 tiles, 9.7 us against 12.4), or 2,048 with a single
+// step of contraction (56x56, one image, 24 -> 144, 1,764 tiles: 4.2 us against
+// 4.8; 112x112, 16 -> 96, 4,704 tiles: 6.1 against 4.9).
+bool use_conv1x1_tile(int64_t P, int C, int O) {
+    const int64_t tiles = ((P + 15) / 16) * ((O + 15) / 16);
+    return tiles <= (C <= 32 ? 2048 : 1024);
+}
+
 template <typename T>
 void launch_conv1x1(const void *x, int64_t P, int C, const void *w, const float *b, int O, int act,
                     const void *res, void *y, hipStream_t st, Marks &mk) {
+    if (use_conv1x1_tile(P, C, O)) {
+        constexpr int D = sizeof(T) == 2 ? 8 : 4;
+        const int nog = ((O + 15) / 16 + kWavesPerBlock - 1) / kWavesPerBlock;
+        launch(mk, k_conv1x1_tile<T, D>, dim3(static_cast<unsigned>((P + 15) / 16 * nog)), dim3(kBlock), 0, st,
+               static_cast<const T *>(x), static_cast<int>(P), C, static_cast<const T *>(w), b, O, act,
+               static_cast<const T *>(res), static_cast<T *>(y), nog);
+        return;
+    }
     static const int kOt[] = {12, 8, 6, 4, 2};
     const int nmt = (O + 15) / 16;
     const int64_t ptiles = (P + kPwPos - 1) / kPwPos;
@@ -1230,19 +1254,33 @@ void launch_conv1x1(const void *x, int64_t P, int C, const void *w, const float 
     }
 }
 
-// Output rows per depthwise task: 4 for 16-bit storage, 2 for fp32.
-template <typename T, int S>
-void launch_dwconv_s(const void *x, dynconv_shape in, dynconv_shape out, int C, const void *w, const float *b,
+// Output rows per depthwise task: 4 (16-bit) or 2 where that still gives
+// kDwMinItems workgroups, else fewer: 9 R / (S (R - 1) + 3) fewer tap loads
+// against waves in flight.
+constexpr int64_t kDwMinItems = 1024;
+
+template <typename T, int S, int R>
+void launch_dwconv_r(const void *x, dynconv_shape in, dynconv_shape out, int C, const void *w, const float *b,
                      int act, void *y, hipStream_t st, Marks &mk) {
-    constexpr int R = sizeof(T) == 4 ? 2 : 4;
-    const size_t lds = static_cast<size_t>(9) * C * sizeof(T);
     const int64_t chunks = (static_cast<int64_t>(out.w) * (C / 8) + kBlock - 1) / kBlock;
     int64_t items = static_cast<int64_t>(out.n) * ((out.h + R - 1) / R) * chunks;
     if (items > 4096) items = 4096;
     if (items < 1) items = 1;
-    launch(mk, k_dwconv3x3<T, S, R>, dim3(static_cast<unsigned>(items)), dim3(kBlock), lds, st,
+    launch(mk, k_dwconv3x3<T, S, R>, dim3(static_cast<unsigned>(items)), dim3(kBlock), 0, st,
            static_cast<const T *>(x), in.n, in.h, in.w, C, static_cast<const T *>(w), b, act, static_cast<T *>(y),
            out.h, out.w);
+}
+
+template <typename T, int S>
+void launch_dwconv_s(const void *x, dynconv_shape in, dynconv_shape out, int C, const void *w, const float *b,
+                     int act, void *y, hipStream_t st, Marks &mk) {
+    const int64_t per_row = out.n * ((static_cast<int64_t>(out.w) * (C / 8) + kBlock - 1) / kBlock);
+    if (sizeof(T) == 2 && per_row * ((out.h + 3) / 4) >= kDwMinItems)
+        launch_dwconv_r<T, S, sizeof(T) == 2 ? 4 : 2>(x, in, out, C, w, b, act, y, st, mk);
+    else if (per_row * ((out.h + 1) / 2) >= kDwMinItems)
+        launch_dwconv_r<T, S, 2>(x, in, out, C, w, b, act, y, st, mk);
+    else
+        launch_dwconv_r<T, S, 1>(x, in, out, C, w, b, act, y, st, mk);
 }
 
 template <typename T>
