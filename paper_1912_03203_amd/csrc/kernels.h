@@ -341,15 +341,63 @@ k_rowscan(const int2 *__restrict__ rowcnt, int64_t nrows, int2 *__restrict__ row
 // per-segment counts (LDS); then the active and dilated positions of row h
 // get their ranks from the words, and every active position finds its 9
 // neighbours' ranks among the dilated positions of the three rows.
+// SCAN: rows holds the row counts (k_rowcount) and the workgroup sums those
+// before its own rows itself, which saves k_rowscan's launch; else rows holds
+// k_rowscan's offsets.
+template <bool SCAN>
 __global__ void __launch_bounds__(kBlock)
 k_compact(const uint64_t *__restrict__ words, int N, int H, int W, int r,
-          const int2 *__restrict__ rowoff, int32_t *__restrict__ active,
-          int32_t *__restrict__ dilated, int32_t *__restrict__ nbr) {
+          const int2 *__restrict__ rows, int32_t *__restrict__ active,
+          int32_t *__restrict__ dilated, int32_t *__restrict__ nbr, int32_t *__restrict__ counts) {
     __shared__ uint64_t dw[kWavesPerBlock][3][kMaxSeg];
     __shared__ int segpre[kWavesPerBlock][3][kMaxSeg];
+    __shared__ int2 part[kWavesPerBlock];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int64_t nrows = static_cast<int64_t>(N) * H;
     const int64_t row = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + wave;
-    if (row >= static_cast<int64_t>(N) * H) return;  // uniform per wave; no block barrier below
+    int2 base = make_int2(0, 0);  // (active, dilated) positions before the row
+    int dil_off[3];               // dilated positions before rows h-1, h, h+1
+    if constexpr (SCAN) {
+        const int row0 = static_cast<int>(blockIdx.x) * kWavesPerBlock;
+        int a = 0, d = 0;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < row0; i += kBlock) {
+            const int2 v = rows[i];
+            a += v.x;
+            d += v.y;
+        }
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            a += __shfl_xor(a, off);
+            d += __shfl_xor(d, off);
+        }
+        if (lane == 0) part[wave] = make_int2(a, d);
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWavesPerBlock; ++w) {
+            base.x += part[w].x;
+            base.y += part[w].y;
+        }
+        if (row >= nrows) return;  // uniform per wave; no block barrier below
+        for (int64_t q = row0; q < row; ++q) {
+            base.x += rows[q].x;
+            base.y += rows[q].y;
+        }
+        const int2 own = rows[row];
+        dil_off[0] = base.y - (row > 0 ? rows[row - 1].y : 0);
+        dil_off[1] = base.y;
+        dil_off[2] = base.y + own.y;
+        if (row == nrows - 1 && lane == 0) {
+            counts[0] = base.x + own.x;
+            counts[1] = base.y + own.y;
+        }
+    } else {
+        if (row >= nrows) return;  // uniform per wave; no block barrier below
+        base = rows[row];
+        dil_off[0] = row > 0 ? rows[row - 1].y : 0;
+        dil_off[1] = base.y;
+        dil_off[2] = rows[row + 1].y;  // nrows + 1 offsets
+    }
     const int h = static_cast<int>(row % H);
     const int nseg = (W + kWave - 1) / kWave;
 
@@ -388,7 +436,6 @@ k_compact(const uint64_t *__restrict__ words, int N, int H, int W, int r,
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
-    const int2 base = rowoff[row];
     const uint64_t lt = lanemask_lt(lane);
     int pre_a = 0;
     for (int seg = 0; seg < nseg; ++seg) {
@@ -412,7 +459,7 @@ k_compact(const uint64_t *__restrict__ words, int N, int H, int W, int r,
                     const uint64_t wd = dw[wave][q][sg];
                     if ((wd >> bit) & 1ull) {
                         const uint64_t below = (bit == 0) ? 0ull : (wd & (~0ull >> (kWave - bit)));
-                        j = rowoff[row + dh].y + segpre[wave][q][sg] + __popcll(below);
+                        j = dil_off[q] + segpre[wave][q][sg] + __popcll(below);
                     }
                 }
                 out[k] = j;
@@ -438,9 +485,15 @@ __global__ void __launch_bounds__(kBlock)
 k_expand(const T *__restrict__ x, int C, int E, const T *__restrict__ w1,
          const float *__restrict__ b1, int act1, const int32_t *__restrict__ dil,
          const int32_t *__restrict__ counts, int64_t dense_rows, T *__restrict__ h1, int eslab,
-         int grid_per_slab) {
+         int grid_per_slab, const uint4 *__restrict__ cp_src, uint4 *__restrict__ cp_dst, int64_t cp_n) {
     typedef mma<T> M;
     extern __shared__ __align__(16) unsigned char ex_lds[];
+    // the identity path of an out-of-place block, which k_dw_project adds to at
+    // the active rows: copied here instead of in a launch of its own
+    if (!DENSE)
+        for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < cp_n;
+             i += static_cast<int64_t>(gridDim.x) * kBlock)
+            cp_dst[i] = cp_src[i];
     // sparse: P_d from the device, clamped to the capacity N*H*W (= dense_rows)
     const int64_t nrows = DENSE ? dense_rows : min(max(static_cast<int64_t>(counts[1]), int64_t{0}), dense_rows);
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
