@@ -652,6 +652,14 @@ k_conv3x3(const T *__restrict__ x, int N, int H, int W, int Ci, int stride, cons
 // ranges of OT tiles of 16.  Accumulation from the bias in kk order (32 at a
 // time on the matrix core); the taps' (dh, dw, c) per kk come from a small
 // LDS table.  Dynamic shared memory: O (32 KS + 8) elements + 32 KS ints.
+// With one contraction step and 3 Ci >= 8 (the stem: Ci = 3) the 8 values of a
+// fragment lie in at most two kernel rows, 3 Ci consecutive elements each in
+// memory, so a lane reads two 16-byte windows, placed so that value u of
+// either is kk = 8 g + u of its row, and picks by masks; positions at the
+// border or at the tensor's end gather value by value.  8 two-byte loads with
+// their LDS table reads and bounds took 41.7 us for 64 x 224x224x3 -> 112x112x32
+// (70 MB), the windows 27.5.
+// A wave takes tiles of 16 output columns of one row.
 template <typename T, int KS, int OT>
 __global__ void __launch_bounds__(kBlock)
 k_conv3x3_mfma(const T *__restrict__ x, int N, int H, int W, int Ci, int stride, const T *__restrict__ w,
@@ -675,31 +683,65 @@ k_conv3x3_mfma(const T *__restrict__ x, int N, int H, int W, int Ci, int stride,
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int r = lane % 16, g = lane / 16;
     const float lo = act_lo(act), hi = act_hi(act);
-    const int64_t total = static_cast<int64_t>(N) * Ho * Wo;
-    const int64_t tiles = (total + 63) / 64;
     const int nmt = (O + 15) / 16;
-    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        const int64_t q = t * 64 + wave * 16 + r;  // this lane's output position (B column)
-        const bool qin = q < total;
-        const int64_t qq = qin ? q : 0;
-        const int64_t ni = qq / Wo;
-        const int j = static_cast<int>(qq - ni * Wo);
-        const int n = static_cast<int>(ni / Ho), i = static_cast<int>(ni - static_cast<int64_t>(n) * Ho);
+    const uint32_t segs = (Wo + 15) / 16, tiles = static_cast<uint32_t>(N) * Ho * segs;
+    // this lane's two windows (one step): element offsets from the position's
+    // first tap, and the masks of the values taken from each
+    const int rl = 3 * Ci, kk0 = 8 * g, kh0 = kk0 / rl, off0 = kk0 - kh0 * rl;
+    const int n0 = min(8, rl - off0);
+    const bool windows = KS == 1 && rl >= 8;
+    const int64_t run0 = kh0 < 3 ? static_cast<int64_t>(kh0) * W * Ci + off0 : 0;
+    const int64_t run1 = kh0 < 2 ? static_cast<int64_t>(kh0 + 1) * W * Ci - n0 : 0;
+    uint32_t m0[4], m1[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        m0[q] = m1[q] = 0;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            const int u = 2 * q + z;
+            const uint32_t half = z ? 0xffff0000u : 0xffffu;
+            if (kk0 + u < K) (u < n0 ? m0[q] : m1[q]) |= half;
+        }
+    }
+    struct __attribute__((packed, aligned(2))) window {
+        uint32_t v[4];
+    };
+    const T *x_end = x + static_cast<int64_t>(N) * H * W * Ci;
+    const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + wave);
+    for (uint32_t t = wave0; t < tiles; t += gridDim.x * kWavesPerBlock) {
+        const uint32_t row = t / segs;
+        const int n = row / Ho, i = row - n * Ho;
+        const int j = (t - row * segs) * 16 + r;  // this lane's output column
+        const bool qin = j < Wo;
+        const int64_t q = static_cast<int64_t>(row) * Wo + j;
         const int h0 = stride * i - 1, w0 = stride * j - 1;
         const T *img = x + static_cast<int64_t>(n) * H * W * Ci;
         Frag bx[KS];
+        const T *first = img + (static_cast<int64_t>(h0) * W + w0) * Ci;
+        // whole 3 x 3 window inside, and no read past the tensor: the last one
+        // ends 8 elements after the start of a run of the last kernel row
+        if (windows && qin && h0 >= 0 && h0 + 3 <= H && w0 >= 0 && w0 + 3 <= W &&
+            first + (2 * static_cast<int64_t>(W) * Ci + rl + 8) <= x_end) {
+            const window a = *reinterpret_cast<const window *>(first + run0);
+            const window c = *reinterpret_cast<const window *>(first + run1);
+            window v;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            float v[8];
+            for (int z = 0; z < 4; ++z) v.v[z] = (a.v[z] & m0[z]) | (c.v[z] & m1[z]);
+            bx[0] = __builtin_bit_cast(Frag, v);
+        } else {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int e = tap[ks * 32 + 8 * g + u];
-                const int hh = h0 + (e & 3), ww = w0 + ((e >> 2) & 3), c = e >> 4;
-                v[u] = (qin && e >= 0 && hh >= 0 && hh < H && ww >= 0 && ww < W)
-                           ? static_cast<float>(img[(static_cast<int64_t>(hh) * W + ww) * Ci + c])
-                           : 0.0f;
+            for (int ks = 0; ks < KS; ++ks) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int e = tap[ks * 32 + 8 * g + u];
+                    const int hh = h0 + (e & 3), ww = w0 + ((e >> 2) & 3), c = e >> 4;
+                    v[u] = (qin && e >= 0 && hh >= 0 && hh < H && ww >= 0 && ww < W)
+                               ? static_cast<float>(img[(static_cast<int64_t>(hh) * W + ww) * Ci + c])
+                               : 0.0f;
+                }
+                bx[ks] = M::pack(v);
             }
-            bx[ks] = M::pack(v);
         }
         for (int ob = 0; ob < nmt; ob += OT) {
             floatx4 acc[OT];

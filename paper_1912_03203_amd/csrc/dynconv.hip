@@ -1308,8 +1308,8 @@ template <typename T, int KS, int OT>
 void launch_conv3x3_mfma(const void *x, dynconv_shape in, dynconv_shape out, const dynconv_layer &L, void *y,
                          hipStream_t st, Marks &mk) {
     const size_t lds = static_cast<size_t>(L.c_out) * (KS * 32 + 8) * sizeof(T) + 4 * 32 * KS;
-    int64_t grid = (positions(out) + 63) / 64;
-    if (grid > 8192) grid = 8192;
+    int64_t grid = (static_cast<int64_t>(out.n) * out.h * ((out.w + 15) / 16) + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (grid > 2048) grid = 2048;  // 8 workgroups per compute unit, the weights staged once each
     if (grid < 1) grid = 1;
     launch(mk, k_conv3x3_mfma<T, KS, OT>, dim3(static_cast<unsigned>(grid)), dim3(kBlock), lds, st,
            static_cast<const T *>(x), in.n, in.h, in.w, L.c_in, L.stride, static_cast<const T *>(L.w), L.b,

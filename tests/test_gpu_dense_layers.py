@@ -63,3 +63,18 @@ def test_depthwise_block(dtype, stride, n, h, w, c):
          "w3": inputs.round_to_storage(rng.normal(0, 0.2, (16, c)), dtype), "b3": rng.normal(0, 0.1, 16).astype(np.float32)}
     want = onet.dense_block(x.transpose(0, 3, 1, 2).astype(np.float64), L)
     check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("n,h,w,ci,o", [(1, 1, 1, 3, 8), (2, 3, 3, 3, 16), (1, 2, 40, 3, 32), (3, 33, 35, 3, 32),
+                                        (2, 18, 67, 3, 72), (1, 9, 21, 1, 16), (1, 9, 21, 2, 16), (2, 9, 21, 4, 24)])
+def test_conv3x3(dtype, stride, n, h, w, ci, o):
+    """The stem's two read windows per lane (3 input channels), the border and
+    the tensor's end, and the value-by-value gather of other widths."""
+    rng = inputs.rng_for(h * w + ci)
+    x = inputs.round_to_storage(rng.standard_normal((n, h, w, ci)), dtype)
+    L = {"kind": "conv3x3", "w": inputs.round_to_storage(rng.normal(0, 0.2, (o, ci, 3, 3)), dtype),
+         "b": rng.normal(0, 0.1, o).astype(np.float32), "stride": stride, "act": 2}
+    want = onet.conv3x3(x.transpose(0, 3, 1, 2).astype(np.float64), L["w"], L["b"], stride, 2)
+    check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
