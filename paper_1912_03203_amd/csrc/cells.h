@@ -14,9 +14,14 @@
 //      needed positions on the matrix cores (the bias is the accumulator's
 //      start), activation, stored at the position's slot of the wave's
 //      region array (slots outside the image hold zeros: the depthwise
-//      padding); the depthwise 3x3 at the active positions reads its 9 taps
-//      at fixed slot offsets; its output is the B operand of the projection,
-//      accumulated over the slices on the matrix cores;
+//      padding).  Depthwise 3x3: lane (r, g) takes both rows of image column
+//      r % 8 for 4 hidden channels, which reads 12 taps of 8 bytes instead of
+//      2 x 9 of them and 9 weights of 8 bytes (a lane per position and 8
+//      channels: 9 taps and 9 weights of 16 bytes, or, with the weights
+//      broadcast by DPP, 36 moves); lanes r and r + 8 then exchange halves
+//      (4 DPP moves), so that each holds the 8 channels of its own position,
+//      the B operand of the projection, accumulated over the slices on the
+//      matrix cores;
 //   3. epilogue: y = x + F at the active positions, x elsewhere, stored for
 //      every position of the cell; then the next block's mask unit on the
 //      stored values (the fp32 multiply-add chain of k_mask), and the
@@ -31,6 +36,12 @@
 // share of the grid (copy and next mask unit, one position per lane), so
 // the copies overlap the active work of the other waves.  A dense region of
 // the mask is spread over many CUs, and the span follows the active work.
+// Bound by vector issue: a cell's slice issues about 150 vector instructions,
+// 72 of them the depthwise's multiply-adds (192 before the two-row lanes in
+// dense launches, and 120 conversions more in bf16).  Measured per block: dense
+// 200 x 64x64x32 bf16 177 -> 139 us; gated at 0.25, 768 x 64x64x32 bf16 412 -> 385
+// us, 32 x 64x64x32 fp16 15.7 -> 15.3; one 32 x 56x56x24 block with its counts
+// 18.3 -> 17.2.
 // The arithmetic of every output element is the one of the kernel chain
 // (k_expand, k_dw_project): the same operand fragments, summation order and
 // roundings.  Input and output must be different buffers (a cell's ring is
@@ -71,7 +82,7 @@ struct CellWeights {
     alignas(16) T w1[kCellMaxE][kCellMaxC + 8];   // expansion rows e, channels fastest (zero past C, E)
     alignas(16) T w3[kCellMaxC][kCellMaxE + 8];   // projection rows c, hidden fastest (zero past C, E)
     alignas(16) T w2[9][kCellMaxE + 8];           // depthwise taps, transposed (zero past E); the
-                                                  // padding puts the nine rows on distinct LDS banks
+                                                  // padding spreads the nine rows over the LDS banks
     alignas(16) float b1[kCellMaxE];
     alignas(16) float b2[kCellMaxE];
     alignas(16) float b3[kCellMaxC];
@@ -79,10 +90,8 @@ struct CellWeights {
 };
 
 // A slice of the expansion in region layout: slot (rr, cc) at byte
-// rr * kRegPitch + cc * kSlotBytes.  The 96 padding bytes per region row put
-// the two image rows of a 16-position tile on distinct LDS banks (a 16-byte
-// read of 16 lanes touches every bank once); a spare slot at the end takes
-// the padding lanes of the last tile.
+// rr * kRegPitch + cc * kSlotBytes, 96 padding bytes per region row; a spare
+// slot at the end takes the padding lanes of the last tile.
 constexpr int kSlotBytes = kChunkPad * 2;                 // 80: 32 channels + 8 padding, 16-bit
 constexpr int kRegPitch = kRegCols * kSlotBytes + 96;     // 896
 constexpr int kSpareSlot = kRegRows * kRegPitch;          // byte offset of the spare slot
@@ -93,21 +102,7 @@ struct CellWaveLds {
     alignas(16) char h1[kSpareSlot + kSlotBytes];  // the region array of one slice
     alignas(16) T xr[kRegSlots][kChunkPad];        // x at the region slots; the own slots become y
     int8_t need[48];
-    int8_t act[kCellOwn];
 };
-
-// Lane S of each 16-lane row of the wave, to every lane of that row (DPP
-// row_newbcast, one move per register).
-template <int S>
-__device__ __forceinline__ uint4 row_bcast16(uint4 v) {
-    static_assert(S >= 0 && S < 16, "source lane within the row");
-    uint4 o;
-    o.x = __builtin_amdgcn_mov_dpp(v.x, 0x150 + S, 0xf, 0xf, false);
-    o.y = __builtin_amdgcn_mov_dpp(v.y, 0x150 + S, 0xf, 0xf, false);
-    o.z = __builtin_amdgcn_mov_dpp(v.z, 0x150 + S, 0xf, 0xf, false);
-    o.w = __builtin_amdgcn_mov_dpp(v.w, 0x150 + S, 0xf, 0xf, false);
-    return o;
-}
 
 // A 16-byte store that the next launch reads, not this one: nontemporal, so
 // that the lines leave the L2 as they are written rather than at the end of
@@ -417,7 +412,6 @@ k_block_cells(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
             const int nneed = __popcll(NEED);
             const int ntn = (nneed + 15) >> 4;
             if ((NEED >> lane) & 1ull) V.need[__popcll(NEED & lt)] = static_cast<int8_t>(lane);
-            if ((A >> lane) & 1ull) V.act[__popcll(A & lt)] = static_cast<int8_t>(lane);
             if (lane < kRegSlots && !inimg) {  // the depthwise's zero padding
                 uint4 *z = reinterpret_cast<uint4 *>(V.h1 + slot_off(lane));
 #pragma unroll
@@ -437,16 +431,19 @@ k_block_cells(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
                 const int qx = (q >= 0) ? q : kCellFirstOwn;  // an in-image slot
                 bx[t] = (t < ntn && 8 * g < C) ? M::load(&V.xr[qx][8 * g]) : M::zero();
             }
-            // the tile's active position of this lane (padding lanes: -1)
-            const int aq = (r < __popcll(A)) ? static_cast<int>(V.act[r]) : -1;
+            // column r of the tile is own position r, at this region slot (-1 when
+            // inactive: its sums are never stored)
+            const int rslot = (r / kCellCols + 1) * kRegCols + r % kCellCols + 1;
+            const int aq = ((A >> rslot) & 1ull) ? rslot : -1;
             floatx4 acc[2];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) acc[mt][v] = L.w.b3[mt * 16 + 4 * g + v];
-            // padding lanes compute around an own slot; their projection
-            // columns are never stored
-            const char *own = V.h1 + slot_off(aq >= 0 ? aq : kCellFirstOwn) + 16 * g;
+            // the depthwise of this lane: the two positions of image column r % 8,
+            // hidden channels 8 g + 4 (r / 8) .. + 3 of the slice
+            const int hsel = r / kCellCols;
+            const char *tap0 = V.h1 + (r % kCellCols) * kSlotBytes + 16 * g + 8 * hsel;
 
             for (int ec = 0; ec < nsl; ++ec) {
                 const int eb = ec * kChunk;
@@ -455,34 +452,14 @@ k_block_cells(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
                     else if (ec == 4) __builtin_amdgcn_s_setprio(1);
                 }
                 // ---- 2a. expansion of the needed slots into the region array:
-                // the tiles' products issued back to back, then activated
-                // the slice's per-channel constants.  Dense launches (four busy
-                // waves per SIMD, the LDS the tighter resource): one 16-byte
-                // read per lane (lane r of a 16-lane row: tap r's depthwise
-                // weights for r < 9, the depthwise bias for r = 9, 10, the
-                // expansion bias of the two output tiles for r = 11, 12),
-                // broadcast within the row by DPP moves.  Gated launches (about
-                // three busy waves per SIMD, the vector ALU the tighter
-                // resource): row-wide broadcast reads from LDS instead, with
-                // no vector instruction.  The values are the same.
-                const uint4 pk = !DENSE ? make_uint4(0, 0, 0, 0) : *reinterpret_cast<const uint4 *>(
-                    r < 9 ? reinterpret_cast<const char *>(&L.w.w2[r][eb + 8 * g])
-                    : r < 11 ? reinterpret_cast<const char *>(&L.w.b2[eb + 8 * g + 4 * (r - 9)])
-                             : reinterpret_cast<const char *>(&L.w.b1[eb + 16 * (r == 12) + 4 * g]));
+                // the tiles' products issued back to back, then activated.  The
+                // slice's constants come by row-wide broadcast reads from LDS.
                 typename M::frag a1[2];
                 floatx4 bi[2];
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
                     a1[m] = M::load(&L.w.w1[eb + m * 16 + r][8 * g]);
-                    if (!DENSE) {
-                        bi[m] = *reinterpret_cast<const floatx4 *>(&L.w.b1[eb + m * 16 + 4 * g]);
-                    } else {
-                        const uint4 b = (m == 0) ? row_bcast16<11>(pk) : row_bcast16<12>(pk);
-                        bi[m][0] = __uint_as_float(b.x);
-                        bi[m][1] = __uint_as_float(b.y);
-                        bi[m][2] = __uint_as_float(b.z);
-                        bi[m][3] = __uint_as_float(b.w);
-                    }
+                    bi[m] = *reinterpret_cast<const floatx4 *>(&L.w.b1[eb + m * 16 + 4 * g]);
                 }
                 auto expand = [&](auto ntiles) {
                     constexpr int NTL = decltype(ntiles)::value;
@@ -510,48 +487,43 @@ k_block_cells(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
                 typename M::frag a3[2];
 #pragma unroll
                 for (int mt = 0; mt < 2; ++mt) a3[mt] = M::load(&L.w.w3[mt * 16 + r][eb + 8 * g]);
-                // all nine taps and their weights requested before the first
+                // the twelve taps of both positions requested before the first
                 // multiply-add (the LDS latency is paid once per slice)
-                typename io<T>::vec8 tv[9];
+                typedef T quad_t __attribute__((ext_vector_type(4)));
+                quad_t tv[4][3];
 #pragma unroll
-                for (int t = 0; t < 9; ++t)
-                    tv[t] = io<T>::raw8(reinterpret_cast<const T *>(
-                        own + (t / 3 - 1) * kRegPitch + (t % 3 - 1) * kSlotBytes));
-                float s[8];
-                if (!DENSE) {
-                    const floatx4 lo = *reinterpret_cast<const floatx4 *>(&L.w.b2[eb + 8 * g]);
-                    const floatx4 hi = *reinterpret_cast<const floatx4 *>(&L.w.b2[eb + 8 * g + 4]);
-                    s[0] = lo[0]; s[1] = lo[1]; s[2] = lo[2]; s[3] = lo[3];
-                    s[4] = hi[0]; s[5] = hi[1]; s[6] = hi[2]; s[7] = hi[3];
-                } else {
-                    const uint4 lo = row_bcast16<9>(pk), hi = row_bcast16<10>(pk);
-                    s[0] = __uint_as_float(lo.x); s[1] = __uint_as_float(lo.y);
-                    s[2] = __uint_as_float(lo.z); s[3] = __uint_as_float(lo.w);
-                    s[4] = __uint_as_float(hi.x); s[5] = __uint_as_float(hi.y);
-                    s[6] = __uint_as_float(hi.z); s[7] = __uint_as_float(hi.w);
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        tv[i][j] = *reinterpret_cast<const quad_t *>(tap0 + i * kRegPitch + j * kSlotBytes);
+                const int ce = eb + 8 * g + 4 * hsel;
+                const floatx4 b2v = *reinterpret_cast<const floatx4 *>(&L.w.b2[ce]);
+                floatx4 s0 = b2v, s1 = b2v;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const quad_t wk = *reinterpret_cast<const quad_t *>(&L.w.w2[t][ce]);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        s0[u] = __builtin_fmaf(static_cast<float>(wk[u]), static_cast<float>(tv[t / 3][t % 3][u]), s0[u]);
+                        s1[u] = __builtin_fmaf(static_cast<float>(wk[u]), static_cast<float>(tv[t / 3 + 1][t % 3][u]),
+                                               s1[u]);
+                    }
                 }
-                auto tap = [&](auto t) {
-                    constexpr int TT = decltype(t)::value;
-                    const uint4 wb = !DENSE ? *reinterpret_cast<const uint4 *>(&L.w.w2[TT][eb + 8 * g])
-                                            : row_bcast16<TT>(pk);
-                    const typename io<T>::vec8 wk = *reinterpret_cast<const typename io<T>::vec8 *>(&wb);
+                quad_t p0, p1;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        s[u] = __builtin_fmaf(static_cast<float>(wk[u]), static_cast<float>(tv[TT][u]), s[u]);
-                };
-                tap(std::integral_constant<int, 0>());
-                tap(std::integral_constant<int, 1>());
-                tap(std::integral_constant<int, 2>());
-                tap(std::integral_constant<int, 3>());
-                tap(std::integral_constant<int, 4>());
-                tap(std::integral_constant<int, 5>());
-                tap(std::integral_constant<int, 6>());
-                tap(std::integral_constant<int, 7>());
-                tap(std::integral_constant<int, 8>());
-                float hv[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) hv[u] = clamp_act(s[u], lo2, hi2);
-                const typename M::frag bf = M::pack(hv);
+                for (int u = 0; u < 4; ++u) {
+                    p0[u] = static_cast<T>(clamp_act(s0[u], lo2, hi2));
+                    p1[u] = static_cast<T>(clamp_act(s1[u], lo2, hi2));
+                }
+                // lanes r and r + 8 hold channels 0-3 and 4-7 of both positions:
+                // after the exchange each holds all 8 of its own position r
+                const uint2 q0 = __builtin_bit_cast(uint2, p0), q1 = __builtin_bit_cast(uint2, p1);
+                uint4 bq;
+                bq.x = __builtin_amdgcn_update_dpp(q0.x, q1.x, 0x128, 0xf, 0xc, false);  // row_ror:8, lanes 8-15
+                bq.y = __builtin_amdgcn_update_dpp(q0.y, q1.y, 0x128, 0xf, 0xc, false);
+                bq.z = __builtin_amdgcn_update_dpp(q1.x, q0.x, 0x128, 0xf, 0x3, false);  // lanes 0-7
+                bq.w = __builtin_amdgcn_update_dpp(q1.y, q0.y, 0x128, 0xf, 0x3, false);
+                const typename M::frag bf = __builtin_bit_cast(typename M::frag, bq);
 #pragma unroll
                 for (int mt = 0; mt < 2; ++mt) acc[mt] = M::run(a3[mt], bf, acc[mt]);
                 wave_sync();
