@@ -352,69 +352,13 @@ void launch_fused_k(const void *src, void *dst, dynconv_shape s, const dynconv_b
            next ? fm.mask_next : nullptr, fm.band_counts, fm.mask_mode);
 }
 
-// Patches of the channel-parallel one-launch kernel: the cut into nph x npw
-// patches with the least estimated time.  A patch costs a fixed part (staging,
-// lists, the barriers and latencies of its chunks) plus its tiles of 16 needed
-// and own positions; patches beyond one per compute unit queue up.
-WideGeom wide_geom_of(dynconv_shape s, int64_t max_patches, int max_need) {
-    WideGeom best{};
-    double best_cost = 0.0;
-    const int w0 = (s.w + kWideMaxCols - 1) / kWideMaxCols;
-    int last_wu = 0;
-    for (int npw_t = w0; npw_t <= s.w && npw_t < w0 + 16; ++npw_t) {
-        const int wu = (s.w + npw_t - 1) / npw_t;
-        if (wu == last_wu) continue;
-        last_wu = wu;
-        const int npw = (s.w + wu - 1) / wu;
-        const int rmax = std::min({s.h, kWideOwn / wu, kWideSlots / (wu + 2) - 2});
-        if (rmax < 1) continue;
-        int last_r = 0;
-        const int h0 = (s.h + rmax - 1) / rmax;
-        for (int nph_t = h0; nph_t <= s.h && nph_t < h0 + 8; ++nph_t) {
-            const int r = (s.h + nph_t - 1) / nph_t;
-            if (r == last_r) continue;
-            last_r = r;
-            const int nph = (s.h + r - 1) / r;
-            const int64_t patches = static_cast<int64_t>(s.n) * nph * npw;
-            if (patches > max_patches) continue;
-            const int need = (r + std::min(nph - 1, 2)) * (wu + std::min(npw - 1, 2));
-            if (need > max_need) continue;
-            const double load = std::max(1.0, static_cast<double>(patches) / 256.0);
-            const double cost = load * (8 + (need + 15) / 16 + (r * wu + 15) / 16);
-            if (best.R == 0 || cost < best_cost - 1e-9) {
-                best_cost = cost;
-                best.R = r;
-                best.Wu = wu;
-                best.nph = nph;
-                best.npw = npw;
-            }
-        }
-    }
-    if (best.R == 0) return best;  // no cut within max_patches
-    best.slots = (best.R + 2) * (best.Wu + 2);
-    best.m_wp = div20_mul(best.Wu + 2);
-    best.m_wu = div20_mul(best.Wu);
-    return best;
-}
-
-// The x fragments of 8 needed tiles fit the registers up to 96 channels; above
-// that the patches are kept to 4 tiles (64 needed positions).  Where that
-// would take more than max_patches (97 to 128 channels, wide images), to 8.
-WideGeom wide_geom(dynconv_shape s, int64_t max_patches) {
-    WideGeom g = wide_geom_of(s, max_patches, s.c <= 96 ? 128 : 64);
-    if (g.R == 0) g = wide_geom_of(s, max_patches, 128);
-    const int need = (g.R + std::min(g.nph - 1, 2)) * (g.Wu + std::min(g.npw - 1, 2));
-    g.tiles = need <= 32 ? 2 : need <= 64 ? 4 : 8;
-    return g;
-}
-
 template <typename T, bool DENSE, int KS, int EC, int NT, bool ONE>
 void launch_wide_k(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
                    const FusedMasks &fm, WideGeom g, hipStream_t st, Marks &mk) {
     const int npatch = s.n * g.nph * g.npw;
     const int grid = (npatch + 7) / 8 * 8;  // whole groups of 8 (one per XCD)
     g.m_pieces = div20_mul(s.c / 8);
-    const size_t lds = wide_lds_bytes<T, EC, ONE>(s.c, g.slots);
+    const size_t lds = wide_lds_bytes(sizeof(T), WideForm{KS, EC, NT, ONE}, s.c, g.slots);
     auto go = [&](auto kern) {
         launch(mk, kern, dim3(grid), dim3(kWideThreads), lds, st, static_cast<const T *>(src), static_cast<T *>(dst),
                s.n, s.h, s.w, s.c, b->c_hidden, g, fm.shuffle_cb, fm.mask_in, fm.self ? b->w_mask : nullptr,
@@ -432,41 +376,19 @@ void launch_wide_k(const void *src, void *dst, dynconv_shape s, const dynconv_bl
     go(k_block_wide<T, DENSE, KS, false, EC, NT, ONE>);
 }
 
-// The instantiation for the channels, the hidden width and the patches' needed
-// tiles.  EC = 128 hidden channels per chunk halves the barriers and loads
-// each weight once per workgroup; 64 where the registers or (fp32) the LDS
-// don't hold 128, and where 64 are all there are.
+// The instantiation that wide_form names for the channels, the hidden width and
+// the patches' needed tiles.
 template <typename T, bool DENSE>
 void launch_wide(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
                  const FusedMasks &fm, const WideGeom &g, hipStream_t st, Marks &mk) {
-#define DC_WIDE_K(KS, EC, NT, ONE) launch_wide_k<T, DENSE, KS, EC, NT, ONE>(src, dst, s, b, next, fm, g, st, mk)
-    if constexpr (sizeof(T) == 4) {  // at most 64 channels (use_fused)
-        if (s.c <= 32) {
-            if (g.tiles == 8) DC_WIDE_K(1, 64, 8, false);
-            else DC_WIDE_K(1, 64, 4, false);
-        } else {
-            if (g.tiles == 8) DC_WIDE_K(2, 64, 8, false);
-            else DC_WIDE_K(2, 64, 4, false);
-        }
-    } else if (s.c <= 32) {
-        DC_WIDE_K(1, 128, 8, false);
-    } else if (s.c <= 64) {
-        if (b->c_hidden <= 64) DC_WIDE_K(2, 64, 8, true);
-        else if (b->c_hidden <= 128) DC_WIDE_K(2, 128, 8, true);
-        else if (g.tiles == 8) DC_WIDE_K(2, 128, 8, false);
-        else DC_WIDE_K(2, 128, 4, false);
-    } else if (s.c <= 96) {
-        if (g.tiles == 8) DC_WIDE_K(3, 128, 8, false);
-        else DC_WIDE_K(3, 128, 4, false);
-    } else if (s.c <= 128) {
-        if (g.tiles == 8) DC_WIDE_K(4, 64, 8, false);
-        else if (b->c_hidden <= 128) DC_WIDE_K(4, 128, 4, true);
-        else DC_WIDE_K(4, 128, 4, false);
-    } else if (s.c <= 160) {
-        if (g.tiles == 2) DC_WIDE_K(5, 128, 2, false);
-        else DC_WIDE_K(5, 64, 4, false);
+    const WideForm f = wide_form(sizeof(T), s.c, b->c_hidden, g.tiles);
+#define DC_WIDE_K(KS, EC, NT, ONE) \
+    if (f.ks == KS && f.ec == EC && f.nt == NT && f.one == ONE) \
+        return launch_wide_k<T, DENSE, KS, EC, NT, ONE>(src, dst, s, b, next, fm, g, st, mk);
+    if constexpr (sizeof(T) == 4) {
+        DC_WIDE_FORMS_32(DC_WIDE_K)
     } else {
-        DC_WIDE_K(6, 64, 4, false);
+        DC_WIDE_FORMS_16(DC_WIDE_K)
     }
 #undef DC_WIDE_K
 }
@@ -592,9 +514,10 @@ constexpr int32_t kStackFlags = kStackDense | kStackUnfused | kStackGSoftmax;
 int mask_mode_of(int32_t flags) { return (flags & kStackGSoftmax) ? 1 : 0; }
 
 // The one-launch block kernels cover up to 64 channels in fp32, and in
-// fp16/bf16 up to 128 and the whole 32-channel steps up to 192 (160 and 192;
-// MobileNetV2's 7x7x160 pair at batch 64: 151 us on the kernel chain, 48 on one
-// launch per block); wider blocks run the unfused kernel chain.
+// fp16/bf16 up to 128 and the whole 32-channel steps up to 192 (160 and 192,
+// where a cut of the map exists; MobileNetV2's 7x7x160 pair at batch 64: 151 us
+// on the kernel chain, 48 on one launch per block); wider blocks run the unfused
+// kernel chain.
 bool use_fused(dynconv_shape s, dynconv_dtype dt, int32_t flags) {
     if (flags & kStackUnfused) return false;
     if (dt == DYNCONV_F32) return s.c <= kMaxFusedC;
@@ -649,6 +572,10 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
                          dynconv_dtype dt, int32_t flags, bool allow_cells = true) {
     StackLayout L{};
     L.fused = use_fused(s, dt, flags);
+    if (L.fused && s.c > kMaxFusedC16) {
+        L.geom = wide_geom(s, INT64_MAX);
+        L.fused = L.geom.R != 0;  // maps without a cut for these widths: the kernel chain
+    }
     L.cells = allow_cells && L.fused && use_cells(s, dt, blks, n_blocks, flags);
     size_t npos = static_cast<size_t>(positions(s));
     size_t off = 0;
@@ -675,7 +602,6 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
             L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
             if (L.geom.R != 0) L.nbands = s.n * L.geom.nph * L.geom.npw;
         } else {
-            L.geom = wide_geom(s, INT64_MAX);
             L.nbands = s.n * L.geom.nph * L.geom.npw;
             off += align_up(2 * static_cast<size_t>(n_blocks) * L.nbands);
         }

@@ -35,39 +35,13 @@
 
 #include "fused.h"
 #include "kernels.h"
+#include "wide_plan.h"
 
 namespace dynconv {
 
-constexpr int kWideWaves = 8;
-constexpr int kWideThreads = kWideWaves * kWave;
-constexpr int kWideOwn = 64;                   // own positions of a patch: 4 tiles
-constexpr int kWideSlots = 128;                // region slots of a patch: two ballot words
-constexpr int kMaxWideC = 192;                 // the B fragments of x stay in registers
-constexpr int kWideMaxCols = 40;               // Wu
-
-// Patch geometry and the multipliers that replace the divisions by its sizes:
-// i / d == (i * m) >> 20 for i * d < 2^20, m = ceil(2^20 / d).
-struct WideGeom {
-    int R, Wu, nph, npw;
-    int slots;                 // (R + 2) * (Wu + 2)
-    int tiles;                 // tiles of 16 needed slots that the kernel has to hold
-    int m_wp, m_wu, m_pieces;  // by the region row, the own row and the 8-element pieces of an x row
-};
-
-__host__ __device__ inline int div20_mul(int d) { return ((1 << 20) + d - 1) / d; }
+// i / d == (i * m) >> 20 for i * d < 2^20, m = div20_mul(d).
 __device__ __forceinline__ int div20(int i, int m) {
     return static_cast<int>((static_cast<unsigned>(i) * static_cast<unsigned>(m)) >> 20);
-}
-
-// EC hidden channels per chunk (LDS rows of EC + 8), one chunk or more
-template <typename T, int EC, bool ONE>
-__host__ __device__ inline size_t wide_lds_bytes(int C, int slots) {
-    const size_t nbuf = ONE ? 1 : 2;
-    return 256 /* words */ + 2 * (kWideSlots + kWideOwn)                    // lists
-           + nbuf * (9 * EC * sizeof(T) + 4 * EC)                          // depthwise weights, biases
-           + static_cast<size_t>(slots) * (C + 8) * sizeof(T)              // x
-           + nbuf * static_cast<size_t>(slots + 1) * (EC + 8) * sizeof(T)  // H1
-           + nbuf * static_cast<size_t>(kWideOwn) * (EC + 8) * sizeof(T);  // H2
 }
 
 // One bit per region slot, the same in every lane.

@@ -1,0 +1,138 @@
+// wide_plan.h -- host-side plan of the channel-parallel patch kernel (wide.h):
+// the cut of an image into patches, the kernel instantiation for a block, and
+// its LDS.  Host code only, free of HIP, so that a CPU test can sweep it.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "dynconv.h"
+
+namespace dynconv {
+
+constexpr int kWideWaves = 8;
+constexpr int kWideThreads = kWideWaves * 64;
+constexpr int kWideOwn = 64;                   // own positions of a patch: 4 tiles
+constexpr int kWideSlots = 128;                // region slots of a patch: two ballot words
+constexpr int kMaxWideC = 192;                 // the B fragments of x stay in registers
+constexpr int kWideMaxCols = 40;               // Wu
+
+// Patch geometry and the multipliers that replace the divisions by its sizes
+// (div20).
+struct WideGeom {
+    int R, Wu, nph, npw;
+    int slots;                 // (R + 2) * (Wu + 2)
+    int tiles;                 // tiles of 16 needed slots that the kernel has to hold
+    int m_wp, m_wu, m_pieces;  // by the region row, the own row and the 8-element pieces of an x row
+};
+
+inline int div20_mul(int d) { return ((1 << 20) + d - 1) / d; }
+
+// The most positions of one patch whose expansion its depthwise reads: the
+// patch and, where the image goes on, the ring around it.
+inline int wide_need(const WideGeom &g) {
+    return (g.R + std::min(g.nph - 1, 2)) * (g.Wu + std::min(g.npw - 1, 2));
+}
+
+// The cut into nph x npw patches with the least estimated time.  A patch costs
+// a fixed part (staging, lists, the barriers and latencies of its chunks) plus
+// its tiles of 16 needed and own positions; patches beyond one per compute unit
+// queue up.  The search tries the 16 smallest numbers of columns and the 8
+// smallest of rows; R = 0: none of them stays within max_patches and max_need.
+inline WideGeom wide_geom_of(dynconv_shape s, int64_t max_patches, int max_need) {
+    WideGeom best{};
+    double best_cost = 0.0;
+    const int w0 = (s.w + kWideMaxCols - 1) / kWideMaxCols;
+    int last_wu = 0;
+    for (int npw_t = w0; npw_t <= s.w && npw_t < w0 + 16; ++npw_t) {
+        const int wu = (s.w + npw_t - 1) / npw_t;
+        if (wu == last_wu) continue;
+        last_wu = wu;
+        const int npw = (s.w + wu - 1) / wu;
+        const int rmax = std::min({s.h, kWideOwn / wu, kWideSlots / (wu + 2) - 2});
+        if (rmax < 1) continue;
+        int last_r = 0;
+        const int h0 = (s.h + rmax - 1) / rmax;
+        for (int nph_t = h0; nph_t <= s.h && nph_t < h0 + 8; ++nph_t) {
+            const int r = (s.h + nph_t - 1) / nph_t;
+            if (r == last_r) continue;
+            last_r = r;
+            WideGeom g{};
+            g.R = r;
+            g.Wu = wu;
+            g.nph = (s.h + r - 1) / r;
+            g.npw = npw;
+            const int64_t patches = static_cast<int64_t>(s.n) * g.nph * npw;
+            if (patches > max_patches) continue;
+            const int need = wide_need(g);
+            if (need > max_need) continue;
+            const double load = std::max(1.0, static_cast<double>(patches) / 256.0);
+            const double cost = load * (8 + (need + 15) / 16 + (r * wu + 15) / 16);
+            if (best.R == 0 || cost < best_cost - 1e-9) {
+                best_cost = cost;
+                best = g;
+            }
+        }
+    }
+    if (best.R == 0) return best;
+    best.slots = (best.R + 2) * (best.Wu + 2);
+    best.m_wp = div20_mul(best.Wu + 2);
+    best.m_wu = div20_mul(best.Wu);
+    return best;
+}
+
+// The x fragments of 8 needed tiles (128 positions) fit the registers up to 96
+// channels.  Above that the patches are kept to 4 tiles; up to 128 channels
+// there is a form with 8 tiles and smaller chunks for the maps on which the
+// search finds no such cut (from about 100 positions a side, or wide strips).
+// Above 128 channels no form holds 8 tiles, and such maps get no cut (R = 0).
+inline WideGeom wide_geom(dynconv_shape s, int64_t max_patches) {
+    WideGeom g = wide_geom_of(s, max_patches, s.c <= 96 ? 128 : 64);
+    if (g.R == 0 && s.c > 96 && s.c <= 128) g = wide_geom_of(s, max_patches, 128);
+    if (g.R == 0) return g;
+    const int need = wide_need(g);
+    g.tiles = need <= 32 ? 2 : need <= 64 ? 4 : 8;
+    return g;
+}
+
+// A kernel instantiation: steps of 32 input channels, hidden channels per
+// chunk, tiles of 16 needed positions held, whether one chunk is all there is.
+struct WideForm {
+    int ks, ec, nt;
+    bool one;
+};
+#define DC_WIDE_FORMS_32(X) X(1, 64, 4, false) X(1, 64, 8, false) X(2, 64, 4, false) X(2, 64, 8, false)
+#define DC_WIDE_FORMS_16(X)                                                                            \
+    X(1, 128, 8, false) X(2, 64, 8, true) X(2, 128, 8, true) X(2, 128, 4, false) X(2, 128, 8, false)   \
+    X(3, 128, 4, false) X(3, 128, 8, false) X(4, 128, 4, true) X(4, 128, 4, false) X(4, 64, 8, false)  \
+    X(5, 128, 2, false) X(5, 64, 4, false) X(6, 64, 4, false)
+
+// The instantiation for the element size, the channels, the hidden width and
+// the patches' needed tiles.  128 hidden channels per chunk halve the barriers
+// and load each weight once per workgroup; 64 where the registers or (fp32) the
+// LDS don't hold 128, and where 64 are all there are.
+inline WideForm wide_form(size_t elem, int c, int e, int tiles) {
+    const bool t8 = tiles == 8;
+    if (elem == 4) return {c <= 32 ? 1 : 2, 64, t8 ? 8 : 4, false};
+    if (c <= 32) return {1, 128, 8, false};
+    if (c <= 64) return e <= 64 ? WideForm{2, 64, 8, true} : e <= 128 ? WideForm{2, 128, 8, true}
+                                                                      : WideForm{2, 128, t8 ? 8 : 4, false};
+    if (c <= 96) return {3, 128, t8 ? 8 : 4, false};
+    if (c <= 128) return t8 ? WideForm{4, 64, 8, false} : WideForm{4, 128, 4, e <= 128};
+    if (c <= 160) return tiles == 2 ? WideForm{5, 128, 2, false} : WideForm{5, 64, 4, false};
+    return {6, 64, 4, false};
+}
+
+// Dynamic LDS of a form at C channels: rows of EC + 8 hidden channels.
+inline size_t wide_lds_bytes(size_t elem, const WideForm &f, int C, int slots) {
+    const size_t nbuf = f.one ? 1 : 2, row = static_cast<size_t>(f.ec) + 8;
+    return 256 /* words */ + 2 * (kWideSlots + kWideOwn)              // lists
+           + nbuf * (9 * static_cast<size_t>(f.ec) * elem + 4 * f.ec)  // depthwise weights, biases
+           + static_cast<size_t>(slots) * (C + 8) * elem               // x
+           + nbuf * static_cast<size_t>(slots + 1) * row * elem        // H1
+           + nbuf * static_cast<size_t>(kWideOwn) * row * elem;        // H2
+}
+
+}  // namespace dynconv

@@ -232,6 +232,25 @@ def test_stack_launch_plans(lib):
     assert lib.dynconv_stack_launch_names(s, arr, 0, 1, 0, 0, None, 0) == -1
 
 
+def stack_names(lib, shape, c, e=192, n=2, dtype=1, flags=0):
+    arr = (dc.Block * n)(*([fake_block(C=c, E=e)] * n))
+    total = lib.dynconv_stack_launch_names(shape, arr, n, dtype, flags, 0, None, 0)
+    out = (ctypes.c_char_p * total)()
+    lib.dynconv_stack_launch_names(shape, arr, n, dtype, flags, 0, out, total)
+    return [x.decode() for x in out]
+
+
+@pytest.mark.parametrize("c", [160, 192])
+@pytest.mark.parametrize("n,h,w", [(1, 112, 112), (1, 109, 109), (1, 48, 160), (8, 112, 112), (2, 20, 600),
+                                   (1, 2, 4096)])
+def test_wide_blocks_on_maps_without_a_cut_take_the_chain(lib, c, n, h, w):
+    """160 and 192 channels: no one-launch kernel holds more than 64 needed
+    positions, and on these maps the cut search finds no patch as small."""
+    assert stack_names(lib, dc.Shape(n, h, w, c), c)[:3] == ["k_copy16", "k_mask", "k_rowcount"]
+    assert stack_names(lib, dc.Shape(n, h, w, c), c, flags=1) == ["k_copy16"] + ["k_expand", "k_dw_project"] * 2
+    assert stack_names(lib, dc.Shape(n, h, w, 128), 128) == ["k_block_fused"] * 2 + ["k_band_counts"]
+
+
 def test_shuffle_stack_validation_and_plans(lib):
     """ShuffleNetV2 units: 116 channels split 58 | 58, the branch padded to 64
     channels (hidden 64); bf16."""

@@ -35,6 +35,12 @@ CASES = [
     ("f16", (5, 7, 7, 160, 960), 0.4, 2),        # 2 needed tiles
     ("bf16", (2, 16, 15, 160, 304), 0.4, 2),     # 4 needed tiles, chunks of 64
     ("f16", (1, 9, 1, 192, 80), 0.5, 1),
+    ("f16", (1, 100, 100, 160, 160), 0.9, 1),    # 4 needed tiles, all of them full
+    ("bf16", (1, 60, 60, 192, 176), 0.9, 1),
+    ("f16", (1, 112, 112, 160, 160), 0.9, 2),    # 160 and 192 channels without a cut: the chain
+    ("bf16", (1, 48, 160, 192, 192), 0.6, 1),
+    ("f16", (2, 20, 600, 160, 176), 0.9, 1),
+    ("bf16", (1, 112, 112, 128, 144), 0.9, 1),   # 97-128 channels, 8 needed tiles, nearly full
     ("f16", (2, 5, 6, 32, 208), 0.4, 2),         # above the cell kernel's hidden width
     ("f32", (1, 7, 3, 8, 16), 0.5, 2),
     ("f32", (2, 16, 17, 32, 192), 0.4, 2),
