@@ -356,11 +356,13 @@ template <typename T, bool DENSE, int KS, int EC, int NT, bool ONE>
 void launch_wide_k(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
                    const FusedMasks &fm, WideGeom g, hipStream_t st, Marks &mk) {
     const int npatch = s.n * g.nph * g.npw;
-    const int grid = (npatch + 7) / 8 * 8;  // whole groups of 8 (one per XCD)
+    const int along = std::min(npatch, kWideGridPatches);
+    // whole groups of 8 (one per XCD)
+    const dim3 grid((along + 7) / 8 * 8, (npatch + kWideGridPatches - 1) / kWideGridPatches);
     g.m_pieces = div20_mul(s.c / 8);
     const size_t lds = wide_lds_bytes(sizeof(T), WideForm{KS, EC, NT, ONE}, s.c, g.slots);
     auto go = [&](auto kern) {
-        launch(mk, kern, dim3(grid), dim3(kWideThreads), lds, st, static_cast<const T *>(src), static_cast<T *>(dst),
+        launch(mk, kern, grid, dim3(kWideThreads), lds, st, static_cast<const T *>(src), static_cast<T *>(dst),
                s.n, s.h, s.w, s.c, b->c_hidden, g, fm.shuffle_cb, fm.mask_in, fm.self ? b->w_mask : nullptr,
                b->b_mask, fm.mask_self, static_cast<const T *>(b->w_expand), b->b_expand, b->act_expand,
                static_cast<const T *>(b->w_dw), b->b_dw, b->act_dw, static_cast<const T *>(b->w_project),

@@ -80,6 +80,28 @@ def test_stack_equals_the_kernel_chain(case, dense):
     assert np.array_equal(y.cpu().view(torch.uint8).numpy(), got[0][0])
 
 
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("c", [40, 96, 160])
+def test_more_patches_than_one_grid_dimension(c, dense):
+    """Many tiny images: 8.5 M patches of 512 threads are more than the 2^32
+    threads of one grid dimension.  Every image is one position, so the
+    depthwise is its centre tap; compared with the kernel chain, byte for byte."""
+    n, e, dt = 8_500_000, 16, torch.float16
+    g = torch.Generator(device="cuda").manual_seed(c)
+    x = torch.randn(n, 1, 1, c, generator=g, device="cuda", dtype=dt)
+    blk = dc.BlockWeights.from_arrays(inputs.block_weights(inputs.rng_for(c), c, e, dtype="f16"), dt)
+    got = []
+    for flags in (0, dc.STACK_UNFUSED):
+        y = torch.full_like(x, float("nan"))
+        counts = None if dense else torch.full((1, 2), -1, dtype=torch.int32, device="cuda")
+        dc.stack_forward(x, y, [blk], flags | (dc.STACK_DENSE if dense else 0), None, counts)
+        torch.cuda.synchronize()
+        got.append((y, counts))
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
+    if not dense:
+        assert torch.equal(got[0][1], got[1][1]) and 0 < int(got[0][1][0, 0]) < n
+
+
 @pytest.mark.parametrize("dtype,c,cp,e", [("bf16", 20, 16, 32), ("f16", 116, 64, 144), ("f32", 34, 24, 32),
                                           ("bf16", 232, 120, 256), ("f16", 312, 160, 160)])
 def test_shuffle_units_equal_the_kernel_chain(dtype, c, cp, e):
