@@ -620,6 +620,14 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
         L.hidden = off;  off += hidden_bytes(s, emax, dt);
     }
     L.total = off;
+    // 160 and 192 channels ran the kernel chain before they had a one-launch
+    // kernel: it takes them only where its scratch is no larger (hidden widths
+    // from about 0.85 times the channels), so that what fits a workspace of a
+    // fixed size stays accepted
+    if (L.fused && s.c > kMaxFusedC16) {
+        const StackLayout chain = stack_layout(s, blks, n_blocks, dt, flags | kStackUnfused, allow_cells);
+        if (L.total > chain.total) return chain;
+    }
     return L;
 }
 

@@ -251,6 +251,19 @@ def test_wide_blocks_on_maps_without_a_cut_take_the_chain(lib, c, n, h, w):
     assert stack_names(lib, dc.Shape(n, h, w, 128), 128) == ["k_block_fused"] * 2 + ["k_band_counts"]
 
 
+@pytest.mark.parametrize("c", [160, 192])
+@pytest.mark.parametrize("e", [16, 96, 160, 1152])
+@pytest.mark.parametrize("n", [1, 3, 1024])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (200, 14, 14), (64, 7, 7), (2, 5, 90), (1, 112, 112)])
+def test_wide_blocks_need_no_more_scratch_than_the_chain(lib, c, e, n, shape):
+    """A caller with scratch of a fixed size (the call without allocation has
+    16 MiB) keeps every stack of these widths that the chain's layout admits."""
+    s, arr = dc.Shape(*shape, c), (dc.Block * n)(*([fake_block(C=c, E=e)] * n))
+    for flags in (0, 1):
+        need = lib.dynconv_stack_workspace_bytes(s, arr, n, 1, flags)
+        assert 0 < need <= lib.dynconv_stack_workspace_bytes(s, arr, n, 1, flags | 2)
+
+
 def test_shuffle_stack_validation_and_plans(lib):
     """ShuffleNetV2 units: 116 channels split 58 | 58, the branch padded to 64
     channels (hidden 64); bf16."""
