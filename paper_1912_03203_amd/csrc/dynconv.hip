@@ -116,6 +116,15 @@ void launch(Marks &mk, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t l
                           static_cast<KArgs>(args)...);
 }
 
+// A one-dimensional grid as x and y (block_xy): a dimension holds fewer than
+// 2^32 threads, and past that a launch leaves the rest out without an error.
+// Whole groups of 8 along x (one per XCD).
+dim3 grid_xy(int64_t blocks) {
+    constexpr int64_t kAlong = int64_t{1} << 22;  // 2^31 threads in workgroups of 512
+    return blocks <= kAlong ? dim3(static_cast<unsigned>(blocks))
+                            : dim3(kAlong, static_cast<unsigned>((blocks + kAlong - 1) / kAlong));
+}
+
 // ------------------------------------------------------------ workspaces
 struct IndexScratch {
     int2 *rowcnt;
@@ -174,18 +183,18 @@ void launch_indices(const uint8_t *mask, dynconv_shape s, int dilate, const dync
                     void *ws, bool scan_launch, hipStream_t st, Marks &mk) {
     IndexScratch sc = carve_index_scratch(ws, s);
     int64_t rows = static_cast<int64_t>(s.n) * s.h;
-    int grid = static_cast<int>((rows + kWavesPerBlock - 1) / kWavesPerBlock);
-    launch(mk, k_rowcount, dim3(grid), dim3(kBlock), 0, st, mask, s.n, s.h, s.w, dilate,
+    const dim3 grid = grid_xy((rows + kWavesPerBlock - 1) / kWavesPerBlock);
+    launch(mk, k_rowcount, grid, dim3(kBlock), 0, st, mask, s.n, s.h, s.w, dilate,
                        sc.rowcnt, sc.words);
     const uint64_t *words = sc.words;
     if (!scan_launch && rows <= kScanRows) {
-        launch(mk, k_compact<true>, dim3(grid), dim3(kBlock), 0, st, words, s.n, s.h, s.w, dilate, sc.rowcnt,
+        launch(mk, k_compact<true>, grid, dim3(kBlock), 0, st, words, s.n, s.h, s.w, dilate, sc.rowcnt,
                idx->active, idx->dilated, idx->nbr, idx->counts);
         return;
     }
     launch(mk, k_rowscan, dim3(1), dim3(kScanThreads), 0, st, sc.rowcnt, rows, sc.rowoff,
                        idx->counts);
-    launch(mk, k_compact<false>, dim3(grid), dim3(kBlock), 0, st, words, s.n, s.h, s.w, dilate, sc.rowoff,
+    launch(mk, k_compact<false>, grid, dim3(kBlock), 0, st, words, s.n, s.h, s.w, dilate, sc.rowoff,
            idx->active, idx->dilated, idx->nbr, idx->counts);
 }
 
@@ -339,10 +348,10 @@ void launch_fused_k(const void *src, void *dst, dynconv_shape s, const dynconv_b
     typedef typename PatchCfgOf<T, MAXC>::type CFG;
     const PatchGeom p = fused_geom_t<T, MAXC>(s);
     const int npatch = s.n * p.nph * p.npw;
-    const int grid = (npatch + 7) / 8 * 8;  // whole groups of 8 (one per XCD)
+    const dim3 grid = grid_xy((static_cast<int64_t>(npatch) + 7) / 8 * 8);
     auto kern = fm.shuffle_cb ? k_block_fused<T, DENSE, MAXKS, MAXMT, MAXC, CFG, true>
                               : k_block_fused<T, DENSE, MAXKS, MAXMT, MAXC, CFG, false>;
-    launch(mk, kern, dim3(grid), dim3(CFG::kThreads), 0, st,
+    launch(mk, kern, grid, dim3(CFG::kThreads), 0, st,
            static_cast<const T *>(src), static_cast<T *>(dst), s.n, s.h, s.w, s.c, b->c_hidden, p.R, p.Wu,
            fm.shuffle_cb, fm.mask_in, fm.self ? b->w_mask : nullptr, b->b_mask, fm.mask_self,
            static_cast<const T *>(b->w_expand), b->b_expand, b->act_expand,
@@ -356,9 +365,7 @@ template <typename T, bool DENSE, int KS, int EC, int NT, bool ONE>
 void launch_wide_k(const void *src, void *dst, dynconv_shape s, const dynconv_block *b, const dynconv_block *next,
                    const FusedMasks &fm, WideGeom g, hipStream_t st, Marks &mk) {
     const int npatch = s.n * g.nph * g.npw;
-    const int along = std::min(npatch, kWideGridPatches);
-    // whole groups of 8 (one per XCD)
-    const dim3 grid((along + 7) / 8 * 8, (npatch + kWideGridPatches - 1) / kWideGridPatches);
+    const dim3 grid = grid_xy((static_cast<int64_t>(npatch) + 7) / 8 * 8);
     g.m_pieces = div20_mul(s.c / 8);
     const size_t lds = wide_lds_bytes(sizeof(T), WideForm{KS, EC, NT, ONE}, s.c, g.slots);
     auto go = [&](auto kern) {

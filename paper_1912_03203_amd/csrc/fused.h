@@ -271,8 +271,9 @@ k_block_fused(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
     // XCD-aware: workgroup i runs on XCD i % 8, so consecutive patches
     // (which share ring rows and columns) go to the same XCD.
     const int per_xcd = (npatch + 7) / 8;
-    const int patch = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (patch >= npatch) return;  // uniform per workgroup
+    const int bid = static_cast<int>(block_xy());
+    const int patch = (bid % 8) * per_xcd + bid / 8;
+    if (bid / 8 >= per_xcd || patch >= npatch) return;  // uniform per workgroup
     const int n = patch / (nph * npw);
     const int h0 = ((patch / npw) % nph) * R;
     const int w0 = (patch % npw) * Wu;

@@ -184,6 +184,11 @@ template <> struct mma<float> {
     }
 };
 
+// The workgroup's number in a grid that grid_xy (dynconv.hip) cut.
+__device__ __forceinline__ int64_t block_xy() {
+    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+}
+
 // Activation as one clamp: kind 0 none, 1 ReLU, 2 ReLU6.  act_lo / act_hi
 // are uniform, so activate() is a single branch-free v_med3.
 __device__ __forceinline__ float act_lo(int kind) { return kind == 0 ? -__builtin_huge_valf() : 0.0f; }
@@ -263,7 +268,7 @@ k_rowcount(const uint8_t *__restrict__ mask, int N, int H, int W, int r, int2 *_
            uint64_t *__restrict__ words) {
     __shared__ uint64_t rows[kWavesPerBlock][7][kMaxSeg];  // rows h-r .. h+r, r <= 3
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + wave;
+    const int64_t row = block_xy() * kWavesPerBlock + wave;
     if (row >= static_cast<int64_t>(N) * H) return;  // uniform per wave; no block barrier below
     const int n = static_cast<int>(row / H), h = static_cast<int>(row % H);
     const int nseg = (W + kWave - 1) / kWave;
@@ -354,7 +359,7 @@ k_compact(const uint64_t *__restrict__ words, int N, int H, int W, int r,
     __shared__ int2 part[kWavesPerBlock];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int64_t nrows = static_cast<int64_t>(N) * H;
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + wave;
+    const int64_t row = block_xy() * kWavesPerBlock + wave;
     int2 base = make_int2(0, 0);  // (active, dilated) positions before the row
     int dil_off[3];               // dilated positions before rows h-1, h, h+1
     if constexpr (SCAN) {

@@ -244,14 +244,13 @@ k_block_wide(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int 
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), lane = tid % kWave;
     const int r = lane % 16, g = lane / 16;
-    const int first = blockIdx.y * kWideGridPatches;
-    const int npatch = min(N * G.nph * G.npw - first, kWideGridPatches);
+    const int npatch = N * G.nph * G.npw;
     // XCD-aware: workgroup i runs on XCD i % 8, so consecutive patches
     // (which share ring rows and columns) go to the same XCD.
     const int per_xcd = (npatch + 7) / 8;
-    const int local = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    if (local >= npatch) return;  // uniform per workgroup
-    const int patch = first + local;
+    const int bid = static_cast<int>(block_xy());
+    const int patch = (bid % 8) * per_xcd + bid / 8;
+    if (bid / 8 >= per_xcd || patch >= npatch) return;  // uniform per workgroup
     const int pimg = G.nph * G.npw;
     const int n = patch / pimg, prem = patch - n * pimg;
     const int pr = prem / G.npw;

@@ -18,8 +18,6 @@ constexpr int kWideOwn = 64;                   // own positions of a patch: 4 ti
 constexpr int kWideSlots = 128;                // region slots of a patch: two ballot words
 constexpr int kMaxWideC = 192;                 // the B fragments of x stay in registers
 constexpr int kWideMaxCols = 40;               // Wu
-constexpr int kWideGridPatches = 1 << 22;      // patches along the grid's x: 2^31 threads, more go to y (a grid
-                                               // dimension holds fewer than 2^32)
 
 // Patch geometry and the multipliers that replace the divisions by its sizes
 // (div20).

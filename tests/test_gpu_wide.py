@@ -81,12 +81,12 @@ def test_stack_equals_the_kernel_chain(case, dense):
 
 
 @pytest.mark.parametrize("dense", [False, True])
-@pytest.mark.parametrize("c", [40, 96, 160])
-def test_more_patches_than_one_grid_dimension(c, dense):
+@pytest.mark.parametrize("c,e", [(40, 16), (96, 16), (160, 160), (32, 208)])
+def test_more_patches_than_one_grid_dimension(c, e, dense):
     """Many tiny images: 8.5 M patches of 512 threads are more than the 2^32
     threads of one grid dimension.  Every image is one position, so the
     depthwise is its centre tap; compared with the kernel chain, byte for byte."""
-    n, e, dt = 8_500_000, 16, torch.float16
+    n, dt = 8_500_000, torch.float16
     g = torch.Generator(device="cuda").manual_seed(c)
     x = torch.randn(n, 1, 1, c, generator=g, device="cuda", dtype=dt)
     blk = dc.BlockWeights.from_arrays(inputs.block_weights(inputs.rng_for(c), c, e, dtype="f16"), dt)
@@ -100,6 +100,22 @@ def test_more_patches_than_one_grid_dimension(c, dense):
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16))
     if not dense:
         assert torch.equal(got[0][1], got[1][1]) and 0 < int(got[0][1][0, 0]) < n
+
+
+def test_more_rows_than_one_grid_dimension():
+    """70 M rows of one position: the index lists take one wave of 64 per row."""
+    n = 70_000_000
+    s = dc.Shape(n, 1, 1, 8)
+    m = (torch.arange(n, device="cuda") % 3 == 0).to(torch.uint8)
+    idx = dc.IndexBuffers.alloc(n)
+    dc.build_indices(m, s, 1, idx, torch.empty(dc.indices_workspace_bytes(s), dtype=torch.uint8, device="cuda"))
+    want = torch.arange(0, n, 3, device="cuda", dtype=torch.int32)
+    p = want.numel()
+    assert idx.counts.tolist() == [p, p]
+    assert torch.equal(idx.active[:p], want) and torch.equal(idx.dilated[:p], want)
+    nbr = idx.nbr[:9 * p].view(p, 9)
+    assert torch.equal(nbr[:, 4], torch.arange(p, device="cuda", dtype=torch.int32))
+    assert bool((nbr[:, [0, 1, 2, 3, 5, 6, 7, 8]] == -1).all())
 
 
 @pytest.mark.parametrize("dtype,c,cp,e", [("bf16", 20, 16, 32), ("f16", 116, 64, 144), ("f32", 34, 24, 32),
