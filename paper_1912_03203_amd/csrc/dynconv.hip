@@ -402,12 +402,15 @@ void launch_wide(const void *src, void *dst, dynconv_shape s, const dynconv_bloc
 #undef DC_WIDE_K
 }
 
+// The widest blocks that k_block_fused is instantiated for.
+int fused_max_c(dynconv_dtype dt) { return dt == DYNCONV_F32 ? 32 : 64; }
+
 template <typename T, bool DENSE>
 void launch_fused(const void *src, void *dst, dynconv_shape s, const dynconv_block *b,
                   const dynconv_block *next, const FusedMasks &fm, hipStream_t st, Marks &mk) {
     if (s.c <= 32)
         launch_fused_k<T, DENSE, 1, 2, 32>(src, dst, s, b, next, fm, st, mk);
-    else if constexpr (sizeof(T) == 2)  // up to 64 channels, 16-bit only (pick_wide)
+    else if constexpr (sizeof(T) == 2)  // fused_max_c
         launch_fused_k<T, DENSE, 2, 4, 64>(src, dst, s, b, next, fm, st, mk);
 }
 
@@ -581,11 +584,19 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
                          dynconv_dtype dt, int32_t flags, bool allow_cells = true) {
     StackLayout L{};
     L.fused = use_fused(s, dt, flags);
-    if (L.fused && s.c > kMaxFusedC16) {
-        L.geom = wide_geom(s, INT64_MAX);
-        L.fused = L.geom.R != 0;  // maps without a cut for these widths: the kernel chain
-    }
     L.cells = allow_cells && L.fused && use_cells(s, dt, blks, n_blocks, flags);
+    if (L.fused && !L.cells) {
+        if (s.c <= kMaxFusedC16) {
+            // per-patch counts: 8 bytes a patch of k_block_fused; the
+            // channel-parallel kernel packs 2 bytes into the same room
+            L.nbands = fused_patch_count(s, dt);
+            L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
+        } else {
+            L.geom = wide_geom(s, INT64_MAX);
+        }
+        // no cut, and a width that k_block_fused has no instantiation for: the kernel chain
+        L.fused = L.geom.R != 0 || s.c <= fused_max_c(dt);
+    }
     size_t npos = static_cast<size_t>(positions(s));
     size_t off = 0;
     if (L.cells) {
@@ -603,17 +614,10 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
         L.mask2 = off;  off += align_up(npos);
         L.counts = off; off += align_up(8 * static_cast<size_t>(n_blocks));
         L.bands = off;
-        if (s.c <= kMaxFusedC16) {
-            // per-patch counts: 8 bytes a patch of k_block_fused; the
-            // channel-parallel kernel packs 2 bytes into the same room
-            L.nbands = fused_patch_count(s, dt);
-            off += align_up(8 * static_cast<size_t>(n_blocks) * L.nbands);
-            L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
-            if (L.geom.R != 0) L.nbands = s.n * L.geom.nph * L.geom.npw;
-        } else {
-            L.nbands = s.n * L.geom.nph * L.geom.npw;
-            off += align_up(2 * static_cast<size_t>(n_blocks) * L.nbands);
-        }
+        off += align_up((s.c <= kMaxFusedC16 ? 8 * static_cast<size_t>(L.nbands)
+                                             : 2 * static_cast<size_t>(s.n) * L.geom.nph * L.geom.npw) *
+                        n_blocks);
+        if (L.geom.R != 0) L.nbands = s.n * L.geom.nph * L.geom.npw;
     } else {
         int emax = 0;
         for (int32_t b = 0; b < n_blocks; ++b)
@@ -809,12 +813,6 @@ struct ShuffleLayout {
     StackLayout in;
 };
 
-bool shuffle_direct(dynconv_shape s, const dynconv_block *br, dynconv_dtype dt, int32_t flags) {
-    dynconv_shape bs = s;
-    bs.c = br[0].c_in;
-    return use_fused(bs, dt, flags) && bs.c <= kMaxFusedC16 && (s.c / 2) * dtype_size(dt) % 4 == 0;
-}
-
 dynconv_shape branch_shape(dynconv_shape s, const dynconv_block *br) {
     dynconv_shape b = s;
     b.c = br[0].c_in;
@@ -826,14 +824,14 @@ ShuffleLayout shuffle_layout(dynconv_shape s, const dynconv_block *br, int32_t n
     const dynconv_shape bs = branch_shape(s, br);
     const size_t npos = static_cast<size_t>(positions(s));
     ShuffleLayout L{};
-    L.direct = shuffle_direct(s, br, dt, flags);
+    L.in = stack_layout(bs, br, n_units, dt, flags, false);
+    L.direct = L.in.fused && bs.c <= kMaxFusedC16 && (s.c / 2) * dtype_size(dt) % 4 == 0;
     const size_t rows = L.direct ? 0 : align_up(npos * bs.c * dtype_size(dt));
     size_t off = 0;
     L.xa = off;    off += rows;
     L.xb = off;    off += rows;
     L.full = off;  off += (n_units > 1) ? align_up(npos * s.c * dtype_size(dt)) : 0;
     L.inner = off;
-    L.in = stack_layout(bs, br, n_units, dt, flags, false);
     off += L.in.total;
     L.total = off;
     return L;

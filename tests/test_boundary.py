@@ -264,6 +264,19 @@ def test_wide_blocks_need_no_more_scratch_than_the_chain(lib, c, e, n, shape):
         assert 0 < need <= lib.dynconv_stack_workspace_bytes(s, arr, n, 1, flags | 2)
 
 
+def test_every_map_up_to_128_channels_has_a_one_launch_plan(lib):
+    """Up to 128 channels (fp32: 64) each block is one kernel whatever the map:
+    the cut search finds a cut within the room for the per-patch counts."""
+    for c, dtype in ((8, 0), (40, 0), (64, 0), (40, 1), (64, 2), (72, 1), (96, 2), (104, 1), (128, 2)):
+        for n in (1, 7, 5000):
+            for h in (1, 2, 3, 7, 13, 28, 50, 112, 300):
+                for w in (1, 2, 5, 9, 28, 33, 40, 41, 112, 299, 4096):
+                    if n * h * w < 10 ** 8:
+                        for e in (16, 384):
+                            assert stack_names(lib, dc.Shape(n, h, w, c), c, e, 2, dtype) == \
+                                ["k_block_fused"] * 2 + ["k_band_counts"], (n, h, w, c, dtype, e)
+
+
 def test_shuffle_stack_validation_and_plans(lib):
     """ShuffleNetV2 units: 116 channels split 58 | 58, the branch padded to 64
     channels (hidden 64); bf16."""
