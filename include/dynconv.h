@@ -235,10 +235,10 @@ size_t dynconv_stack_workspace_bytes(dynconv_shape s, const dynconv_block *blks,
  * all positions (the baseline of Eq. 1).
  *
  * Execution: when s.c <= 64 (fp32), or s.c <= 128 (fp16, bf16), or s.c is 160
- * or 192 (fp16, bf16) and the map is small enough (on larger ones no patch fits
- * the kernel), and DYNCONV_STACK_UNFUSED is not set, each block is ONE kernel over small patches of the image (at most 256
- * positions, at most 40 columns wide), each of which builds the active and
- * halo lists of its patch on chip (ballot ranks in raster order), gathers,
+ * or 192 (fp16, bf16) at maps and batches where one kernel is the faster and
+ * needs no more scratch, and DYNCONV_STACK_UNFUSED is not set, each block is
+ * ONE kernel over small patches of the image (at most 256 positions, at most
+ * 40 columns wide), each of which builds the active and halo lists of its patch on chip (ballot ranks in raster order), gathers,
  * expands, runs the depthwise and the projection, adds the identity path and
  * computes the next block's mask (the first block also runs its own mask
  * unit); blocks alternate between y and a workspace copy.  The per-block

@@ -571,6 +571,32 @@ WideGeom pick_wide(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks,
     return patches <= most ? g : WideGeom{};
 }
 
+// 160 and 192 channels: the channel-parallel kernel, or the kernel chain (R = 0),
+// which loads its weights once for many positions and runs the active ones only.
+// Measured per block, chain / this kernel, us, fp16, hidden 6 C unless noted:
+//   160: 64 x 14x14 (256 patches) density 0.1 107 / 36, dense 225 / 36; gated the
+//     line is at 2,048 patches: 512 x 14x14 (2,048) 198 / 188 at 0.1, hidden 160
+//     84 / 78; 32 x 56x56 (3,136) hidden 160 74 / 92 at 0.1, 105 / 130 at 0.3;
+//     dense up to 64 x 56x56 (6,272 patches) 1975 / 831
+//   192, whose chunks are 64 channels: gated at most 1,024 patches: 256 x 14x14
+//     (1,024) 202 / 178 at 0.1; 48 x 28x28 (1,152) 230 / 282 at 0.3, 512 x 14x14
+//     (2,048) 248 / 307 at 0.1.  Dense 64 x 14x14 274 / 59, 64 x 56x56 2647 / 1391.
+//     Few patches take as long as one, and the chain spreads a hidden width over
+//     the chip: dense 1 x 7x7 (14 patches) 21 / 16 at hidden 192, 39 / 39 at 768,
+//     49 / 55 at 1,152, 1 x 28x28 (70 patches) 52 / 56 at 1,152, 1 x 40x40 (100)
+//     74 / 56; gated at 0.1 1 x 7x7 52 / 49 at 960, 53 / 57 at 1,152, 1 x 14x14 (49)
+//     64 / 57 at 1,152
+WideGeom pick_wide_160(dynconv_shape s, const dynconv_block *blks, int32_t n_blocks, bool dense) {
+    const WideGeom g = wide_geom(s, INT64_MAX);
+    if (g.R == 0) return g;
+    int emax = 0;
+    for (int32_t b = 0; b < n_blocks; ++b) emax = std::max(emax, blks[b].c_hidden);
+    const int64_t patches = static_cast<int64_t>(s.n) * g.nph * g.npw;
+    if (!dense && patches > (s.c <= 160 ? 2048 : 1024)) return WideGeom{};
+    if (s.c > 160 && emax > (dense ? 768 : 960) && patches < (dense ? 96 : 32)) return WideGeom{};
+    return g;
+}
+
 struct StackLayout {
     bool fused, cells;
     WideGeom geom;  // patches of the channel-parallel kernel
@@ -592,7 +618,7 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
             L.nbands = fused_patch_count(s, dt);
             L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
         } else {
-            L.geom = wide_geom(s, INT64_MAX);
+            L.geom = pick_wide_160(s, blks, n_blocks, (flags & kStackDense) != 0);
         }
         // no cut, and a width that k_block_fused has no instantiation for: the kernel chain
         L.fused = L.geom.R != 0 || s.c <= fused_max_c(dt);

@@ -251,6 +251,18 @@ def test_wide_blocks_on_maps_without_a_cut_take_the_chain(lib, c, n, h, w):
     assert stack_names(lib, dc.Shape(n, h, w, 128), 128) == ["k_block_fused"] * 2 + ["k_band_counts"]
 
 
+@pytest.mark.parametrize("shape,c,e,flags,one", [
+    ((512, 14, 14), 160, 960, 0, True), ((513, 14, 14), 160, 960, 0, False), ((513, 14, 14), 160, 960, 1, True),
+    ((32, 56, 56), 160, 160, 0, False), ((64, 56, 56), 160, 160, 1, True), ((1, 7, 7), 160, 960, 0, True),
+    ((256, 14, 14), 192, 1152, 0, True), ((257, 14, 14), 192, 1152, 0, False), ((257, 14, 14), 192, 1152, 1, True),
+    ((1, 7, 7), 192, 960, 0, True), ((1, 7, 7), 192, 976, 0, False), ((1, 14, 14), 192, 1536, 0, True),
+    ((1, 28, 28), 192, 768, 1, True), ((1, 28, 28), 192, 784, 1, False), ((1, 40, 40), 192, 1536, 1, True)])
+def test_wide_blocks_take_the_faster_route(lib, shape, c, e, flags, one):
+    """Both sides of the measured lines between the one-launch kernel and the chain."""
+    names = stack_names(lib, dc.Shape(*shape, c), c, e, 1, 2, flags)
+    assert (names[0] == "k_block_fused") == one
+
+
 @pytest.mark.parametrize("c", [160, 192])
 @pytest.mark.parametrize("e", [16, 96, 160, 1152])
 @pytest.mark.parametrize("n", [1, 3, 1024])
