@@ -547,28 +547,16 @@ bool use_cells(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int
     return true;
 }
 
-// Which patch kernel a stack takes: the channel-parallel one (its patches), or
-// k_block_fused (R = 0), whose patches of 128 or 256 positions amortise their
-// fixed part better once a compute unit has many.  Measured per block, this
-// kernel against k_block_fused, fp16 unless noted:
-//   above 64 channels (only this one now; k_block_fused took up to 128):
-//     64 x 14x14x96: 17.5 / 42 us; 96 x 30x30x96: 71 / 190 us
-//   33 to 64 channels: 64 x 14x14x64, hidden 384 (256 patches): 12.3 / 24.8
-//     us; 96 x 28x28x64 (1,344 patches): 55 / 58, dense 67 / 61; 300 x 28x28x64
-//     (4,200 patches): 153 / 120 us; hidden widths of one chunk (ShuffleNetV2,
-//     bf16, 64 x 28x28, 896 patches): 18 / 25 us
-//   fp32, 64 channels: 16 x 48x48: 83 / 132 us
-//   up to 32 channels, fp32: 1 x 32x32x32 (128 patches): 11.2 / 17.1 us;
-//     16 x 48x48x32 (576 patches): 39 / 30 us
-WideGeom pick_wide(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int32_t n_blocks,
+// Which patch kernel a stack of up to 128 channels takes: the channel-parallel
+// one (its patches), or k_block_fused (R = 0); wide_most_patches has the line.
+WideGeom pick_wide(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int32_t n_blocks, bool dense,
                    int64_t max_patches) {
     const WideGeom g = wide_geom(s, max_patches);
-    if (g.R == 0 || s.c > (dt == DYNCONV_F32 ? 32 : 64)) return g;
-    int emax = 0;
-    for (int32_t b = 0; b < n_blocks; ++b) emax = std::max(emax, blks[b].c_hidden);
+    if (g.R == 0 || s.c > fused_max_c(dt)) return g;
+    WideWork w{};
+    for (int32_t b = 0; b < n_blocks; ++b) w.add(blks[b].c_hidden);
     const int64_t patches = static_cast<int64_t>(s.n) * g.nph * g.npw;
-    const int64_t most = s.c <= 32 ? 256 : emax <= 128 ? INT64_MAX : 1024;
-    return patches <= most ? g : WideGeom{};
+    return patches <= wide_most_patches(s.c, w, dense) ? g : WideGeom{};
 }
 
 // 160 and 192 channels: the channel-parallel kernel, or the kernel chain (R = 0),
@@ -616,7 +604,7 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
             // per-patch counts: 8 bytes a patch of k_block_fused; the
             // channel-parallel kernel packs 2 bytes into the same room
             L.nbands = fused_patch_count(s, dt);
-            L.geom = pick_wide(s, dt, blks, n_blocks, int64_t{4} * L.nbands);
+            L.geom = pick_wide(s, dt, blks, n_blocks, (flags & kStackDense) != 0, int64_t{4} * L.nbands);
         } else {
             L.geom = pick_wide_160(s, blks, n_blocks, (flags & kStackDense) != 0);
         }

@@ -135,4 +135,44 @@ inline size_t wide_lds_bytes(size_t elem, const WideForm &f, int C, int slots) {
            + nbuf * static_cast<size_t>(kWideOwn) * row * elem;        // H2
 }
 
+// The hidden channels of a stack's blocks and their chunks of 128.
+struct WideWork {
+    int64_t blocks, hidden, chunks;
+    int most;  // the widest block's
+    void add(int e) {
+        ++blocks;
+        hidden += e;
+        chunks += (e + 127) / 128;
+        most = std::max(most, e);
+    }
+};
+
+// Up to how many patches of its own a stack that k_block_fused also runs (up to
+// 64 channels, fp32 32) takes the channel-parallel kernel: the larger patches of
+// k_block_fused amortise their fixed part better once a compute unit has many.
+// The time goes in rounds of 256 patches (one workgroup per compute unit) by
+// chunks of 128 hidden channels, that of k_block_fused in rounds of 512 patches by
+// slices of 32, so the line depends on how full the chunks are.  Measured per
+// block, k_block_fused / this kernel, us, fp16 or bf16 unless noted:
+//   one chunk, 64 channels: hidden 64, 64 x 28x28 (896 patches) 14.0 / 12.6 dense,
+//     64 x 56x56 47.7 / 32.1: no line
+//   full chunks (over 0.9), 64 channels: hidden 384, 128 x 14x14 (512 patches) dense
+//     31 / 23, 192 x 14x14 (768) 36 / 34, 64 x 28x28 (896) 35 / 46 and at 0.2 active
+//     36 / 39; hidden 256, 128 x 14x14 23 / 19, 96 x 17x20 (576) dense 26 / 29, at
+//     0.2 26 / 24
+//   0.7 to 0.9: 48 channels, hidden 288, dense: 128 x 14x14 24 / 23, 96 x 17x20 27 / 34
+//   below: 40 channels, hidden 160, dense: 64 x 14x14 (256) 15 / 11, 24 x 28x28 (336)
+//     16 / 20
+//   up to 32 channels, fp32: 1 x 32x32x32 (128 patches) 17.1 / 11.2, 16 x 48x48x32
+//     (576) 30 / 39
+// Wider blocks have no other one-launch kernel (64 x 14x14x96 42 / 17.5, when
+// k_block_fused took up to 128 channels; fp32 16 x 48x48x64 144 / 91).
+inline int64_t wide_most_patches(int c, const WideWork &w, bool dense) {
+    if (c <= 32) return 256;
+    if (w.most <= 128) return INT64_MAX;
+    const double fill = static_cast<double>(w.hidden) / static_cast<double>(std::max<int64_t>(w.chunks, 1) * 128);
+    if (fill > 0.9) return dense && w.hidden < 384 * w.blocks ? 512 : 768;
+    return fill > 0.7 ? 512 : 256;
+}
+
 }  // namespace dynconv

@@ -56,7 +56,28 @@ static void check(dynconv_shape s, int elem) {
     REQUIRE(exact(g.slots * pieces + 4 * per, pieces, div20_mul(pieces)));
 }
 
+static int64_t most(int c, int e, bool dense, int blocks = 1) {
+    WideWork w{};
+    for (int b = 0; b < blocks; ++b) w.add(e);
+    return wide_most_patches(c, w, dense);
+}
+
+// both sides of the measured lines against k_block_fused
+static bool lines() {
+    WideWork mixed{};
+    mixed.add(384);
+    mixed.add(160);  // 5 chunks, 544 of 640 channels
+    return most(64, 64, true) == INT64_MAX && most(40, 128, false) == INT64_MAX && most(64, 384, true, 3) == 768 &&
+           most(64, 384, false) == 768 && most(64, 256, true, 2) == 512 && most(64, 256, false) == 768 &&
+           most(48, 288, true) == 512 && most(48, 192, false) == 512 && most(40, 160, false) == 256 &&
+           most(32, 384, true) == 256 && wide_most_patches(64, mixed, true) == 512;
+}
+
 int main() {
+    if (!lines()) {
+        printf("FAILED lines\n");
+        return 1;
+    }
     static const int hs[] = {1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 14, 17, 20, 28, 31, 40, 48, 56, 64, 100, 109, 112, 128, 144, 224, 500};
     static const int ws[] = {1, 2, 3, 5, 7, 8, 9, 13, 14, 16, 20, 28, 33, 40, 41, 56, 64, 81, 109, 112, 128, 134, 153, 160, 224, 600,
                              1000, 4096};
