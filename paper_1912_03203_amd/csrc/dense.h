@@ -654,19 +654,61 @@ k_conv3x3(const T *__restrict__ x, int N, int H, int W, int Ci, int stride, cons
 // as [O][32 KS + 8] rows in kk order, and the wave walks the outputs in
 // ranges of OT tiles of 16.  Accumulation from the bias in kk order (32 at a
 // time on the matrix core); the taps' (dh, dw, c) per kk come from a small
-// LDS table.  Dynamic shared memory: O (32 KS + 8) elements + 32 KS ints.
-// With one contraction step and 3 Ci >= 8 (the stem: Ci = 3) the 8 values of a
-// fragment lie in at most two kernel rows, 3 Ci consecutive elements each in
-// memory, so a lane reads two 16-byte windows, placed so that value u of
-// either is kk = 8 g + u of its row, and picks by masks; positions at the
-// border or at the tensor's end gather value by value.  8 two-byte loads with
-// their LDS table reads and bounds took 41.7 us for 64 x 224x224x3 -> 112x112x32
-// (70 MB), the windows 27.5.
-// A wave takes tiles of 16 output columns of one row.
-template <typename T, int KS, int OT>
+// LDS table.  Dynamic shared memory: O (32 KS + 8) elements + 32 KS ints, at
+// least 384 bytes (the masks of WIN).
+// A wave takes tiles of 16 consecutive output positions, which may cross rows
+// and images: no width leaves lanes idle.
+//
+// WIN (3 input channels, the stem): the 8 values of a fragment lie in at most
+// two kernel rows, 9 consecutive elements each in memory, so a lane reads two
+// 16-byte windows, placed so that value u of either is kk = 8 g + u of its row,
+// and picks by masks.  Waves with a position at the border narrow the masks and
+// move windows that would reach outside the tensor (shifted back in registers).
+// 8 two-byte loads with their LDS table reads and bounds took 40.2 us for
+// 64 x 224x224x3 -> 112x112x32 (70 MB), the windows 25.7.  With tiles of 16 columns
+// of one row and a gather beside the windows at borders, narrow maps were slower
+// than that: 64 x 224x33 -> 112x17x32 10.2 (gather), 13.2, now 8.5; one 224x224 image
+// 4.8, 5.5, now 4.6.
+struct __attribute__((packed, aligned(2))) half8_bits {
+    uint32_t v[4];
+};
+
+// q / d for q < 2^28: (q * m) >> (32 + s), or q itself for d = 1
+struct Div28 {
+    uint32_t m, s, one;
+};
+inline Div28 div28(uint32_t d) {
+    if (d == 1) return {0, 0, 0xffffffffu};
+    uint32_t l = 1;
+    while ((uint64_t{1} << l) < d) ++l;
+    const uint32_t k = l <= 4 ? 32 : 28 + l;  // 2^28 d <= 2^k, and m below 2^32
+    return {static_cast<uint32_t>(((uint64_t{1} << k) + d - 1) / d), k - 32, 0};
+}
+__device__ __forceinline__ uint32_t quotient(uint32_t q, Div28 d) { return (__umulhi(q, d.m) >> d.s) + (q & d.one); }
+
+// w moved by d elements, zeros moving in: value u of the result is value u - d of w
+__device__ __forceinline__ half8_bits moved(half8_bits w, int d) {
+    half8_bits out;
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {
+        uint32_t pair = 0;
+#pragma unroll
+        for (int z = 0; z < 2; ++z) {
+            uint32_t h = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (u + z - d == k) h = (w.v[k / 2] >> (16 * (k % 2))) & 0xffffu;
+            pair |= h << (16 * z);
+        }
+        out.v[u / 2] = pair;
+    }
+    return out;
+}
+
+template <typename T, int KS, int OT, bool WIN>
 __global__ void __launch_bounds__(kBlock)
 k_conv3x3_mfma(const T *__restrict__ x, int N, int H, int W, int Ci, int stride, const T *__restrict__ w,
-               const float *__restrict__ b, int O, int act, T *__restrict__ y, int Ho, int Wo) {
+               const float *__restrict__ b, int O, int act, T *__restrict__ y, int Ho, int Wo, Div28 dHo, Div28 dWo) {
     typedef mma<T> M;
     typedef typename M::frag Frag;
     constexpr int KP = KS * 32 + 8;  // LDS row pitch of the weights
@@ -678,60 +720,82 @@ k_conv3x3_mfma(const T *__restrict__ x, int N, int H, int W, int Ci, int stride,
         const int o = i / KP, kk = i % KP;
         ws[i] = (kk < K) ? w[(o * Ci + kk % Ci) * 9 + kk / Ci] : static_cast<T>(0.0f);
     }
-    for (int kk = threadIdx.x; kk < 32 * KS; kk += kBlock) {
-        const int k = kk / Ci, c = kk % Ci;
-        tap[kk] = (kk < K) ? ((k / 3) | ((k % 3) << 2) | (c << 4)) : -1;
+    // WIN: the fragment's values of lanes with this g that the window of its first
+    // and of its second kernel row hold, of those the ones in the row's first and
+    // in its last column: masks [g][3][2]
+    uint4 *masks = reinterpret_cast<uint4 *>(tap);
+    if constexpr (WIN) {
+        if (threadIdx.x < 24) {
+            const int mg = threadIdx.x / 6, col = threadIdx.x / 2 % 3, second = threadIdx.x % 2;
+            uint32_t bits[4] = {0, 0, 0, 0};
+            for (int u = 0; u < 8; ++u) {
+                const int kk = 8 * mg + u, at = kk % 9 / 3;  // column of the kernel row
+                if (kk < 27 && (kk / 9 != 8 * mg / 9) == (second == 1) && (col == 0 || at == (col == 1 ? 0 : 2)))
+                    bits[u / 2] |= 0xffffu << (16 * (u % 2));
+            }
+            masks[threadIdx.x] = make_uint4(bits[0], bits[1], bits[2], bits[3]);
+        }
+    } else {
+        for (int kk = threadIdx.x; kk < 32 * KS; kk += kBlock) {
+            const int k = kk / Ci, c = kk % Ci;
+            tap[kk] = (kk < K) ? ((k / 3) | ((k % 3) << 2) | (c << 4)) : -1;
+        }
     }
     __syncthreads();
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int r = lane % 16, g = lane / 16;
     const float lo = act_lo(act), hi = act_hi(act);
     const int nmt = (O + 15) / 16;
-    const uint32_t segs = (Wo + 15) / 16, tiles = static_cast<uint32_t>(N) * Ho * segs;
-    // this lane's two windows (one step): element offsets from the position's
-    // first tap, and the masks of the values taken from each
-    const int rl = 3 * Ci, kk0 = 8 * g, kh0 = kk0 / rl, off0 = kk0 - kh0 * rl;
-    const int n0 = min(8, rl - off0);
-    const bool windows = KS == 1 && rl >= 8;
-    const int64_t run0 = kh0 < 3 ? static_cast<int64_t>(kh0) * W * Ci + off0 : 0;
-    const int64_t run1 = kh0 < 2 ? static_cast<int64_t>(kh0 + 1) * W * Ci - n0 : 0;
-    uint32_t m0[4], m1[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        m0[q] = m1[q] = 0;
-#pragma unroll
-        for (int z = 0; z < 2; ++z) {
-            const int u = 2 * q + z;
-            const uint32_t half = z ? 0xffff0000u : 0xffffu;
-            if (kk0 + u < K) (u < n0 ? m0[q] : m1[q]) |= half;
-        }
+    const uint32_t total = static_cast<uint32_t>(N) * Ho * Wo, tiles = (total + 15) / 16;  // positions fit 28 bits
+    // WIN: element offsets of this lane's two windows from the position's first tap
+    // (32 bits: the tensor has at most 3 2^28 elements); without a second one
+    // the first again
+    const int kk0 = 8 * g, kh0 = kk0 / 9, off0 = kk0 - kh0 * 9, n0 = 9 - off0;
+    const bool two = n0 < 8 && kh0 < 2;
+    const int run0 = kh0 * W * 3 + off0, run1 = two ? (kh0 + 1) * W * 3 - n0 : run0;
+    uint4 m0, m1;
+    if constexpr (WIN) {
+        m0 = masks[6 * g];
+        m1 = masks[6 * g + 1];
     }
-    struct __attribute__((packed, aligned(2))) window {
-        uint32_t v[4];
-    };
-    const T *x_end = x + static_cast<int64_t>(N) * H * W * Ci;
     const uint32_t wave0 = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + wave);
     for (uint32_t t = wave0; t < tiles; t += gridDim.x * kWavesPerBlock) {
-        const uint32_t row = t / segs;
-        const int n = row / Ho, i = row - n * Ho;
-        const int j = (t - row * segs) * 16 + r;  // this lane's output column
-        const bool qin = j < Wo;
-        const int64_t q = static_cast<int64_t>(row) * Wo + j;
+        const bool qin = t * 16 + r < total;
+        const uint32_t q = min(t * 16 + r, total - 1);
+        const uint32_t row = quotient(q, dWo), n = quotient(row, dHo);
+        const int i = row - n * Ho, j = q - row * Wo;
         const int h0 = stride * i - 1, w0 = stride * j - 1;
-        const T *img = x + static_cast<int64_t>(n) * H * W * Ci;
         Frag bx[KS];
-        const T *first = img + (static_cast<int64_t>(h0) * W + w0) * Ci;
-        // whole 3 x 3 window inside, and no read past the tensor: the last one
-        // ends 8 elements after the start of a run of the last kernel row
-        if (windows && qin && h0 >= 0 && h0 + 3 <= H && w0 >= 0 && w0 + 3 <= W &&
-            first + (2 * static_cast<int64_t>(W) * Ci + rl + 8) <= x_end) {
-            const window a = *reinterpret_cast<const window *>(first + run0);
-            const window c = *reinterpret_cast<const window *>(first + run1);
-            window v;
+        if constexpr (WIN) {
+            const int size = N * H * W * 3, first = ((static_cast<int>(n) * H + h0) * W + w0) * 3;
+            const int at0 = first + run0, at1 = first + run1;
+            const int from0 = min(max(at0, 0), size - 8), from1 = min(max(at1, 0), size - 8);
+            half8_bits a = *reinterpret_cast<const half8_bits *>(x + from0);
+            half8_bits c = *reinterpret_cast<const half8_bits *>(x + from1);
+            uint4 s0 = m0, s1 = m1;
+            const bool left = w0 < 0, right = w0 + 3 > W, top = h0 < 0, bottom = h0 + 3 > H;
+            if (__any(left | right | top | bottom)) {
+                const bool in0 = h0 + kh0 >= 0 && h0 + kh0 < H, in1 = h0 + kh0 + 1 < H;
+                const uint4 zero = make_uint4(0, 0, 0, 0);
+                auto narrow = [&](uint4 m, bool in, int second) {
+                    const uint4 l = left ? masks[6 * g + 2 + second] : zero, e = right ? masks[6 * g + 4 + second] : zero;
+                    return in ? make_uint4(m.x & ~(l.x | e.x), m.y & ~(l.y | e.y), m.z & ~(l.z | e.z), m.w & ~(l.w | e.w)) : zero;
+                };
+                s0 = narrow(m0, in0, 0);
+                s1 = narrow(m1, in1, 1);
+            }
+            // windows that would reach outside the tensor were read where it ends
+            if (__any(from0 != at0 || from1 != at1)) {
+                a = moved(a, from0 - at0);
+                c = moved(c, from1 - at1);
+            }
+            half8_bits v;
+            const uint32_t k0[4] = {s0.x, s0.y, s0.z, s0.w}, k1[4] = {s1.x, s1.y, s1.z, s1.w};
 #pragma unroll
-            for (int z = 0; z < 4; ++z) v.v[z] = (a.v[z] & m0[z]) | (c.v[z] & m1[z]);
+            for (int z = 0; z < 4; ++z) v.v[z] = (a.v[z] & k0[z]) | (c.v[z] & k1[z]);
             bx[0] = __builtin_bit_cast(Frag, v);
         } else {
+            const T *img = x + static_cast<int64_t>(n) * H * W * Ci;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 float v[8];
@@ -771,7 +835,7 @@ k_conv3x3_mfma(const T *__restrict__ x, int N, int H, int W, int Ci, int stride,
                     float out[4];
 #pragma unroll
                     for (int v = 0; v < 4; ++v) out[v] = clamp_act(acc[mt][v], lo, hi);
-                    io<T>::store4(y + q * O + o0, out);
+                    io<T>::store4(y + static_cast<int64_t>(q) * O + o0, out);
                 }
             }
         }

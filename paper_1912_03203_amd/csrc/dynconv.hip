@@ -1262,13 +1262,17 @@ void launch_dwconv(const void *x, dynconv_shape in, dynconv_shape out, int C, in
 template <typename T, int KS, int OT>
 void launch_conv3x3_mfma(const void *x, dynconv_shape in, dynconv_shape out, const dynconv_layer &L, void *y,
                          hipStream_t st, Marks &mk) {
-    const size_t lds = static_cast<size_t>(L.c_out) * (KS * 32 + 8) * sizeof(T) + 4 * 32 * KS;
-    int64_t grid = (static_cast<int64_t>(out.n) * out.h * ((out.w + 15) / 16) + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (grid > 2048) grid = 2048;  // 8 workgroups per compute unit, the weights staged once each
-    if (grid < 1) grid = 1;
-    launch(mk, k_conv3x3_mfma<T, KS, OT>, dim3(static_cast<unsigned>(grid)), dim3(kBlock), lds, st,
+    const size_t lds = static_cast<size_t>(L.c_out) * (KS * 32 + 8) * sizeof(T) + std::max(4 * 32 * KS, 384);
+    const int64_t tiles = (positions(out) + 15) / 16;
+    // at most 8 workgroups per compute unit, the weights staged once each
+    const int64_t grid = std::min<int64_t>((tiles + kWavesPerBlock - 1) / kWavesPerBlock, 2048);
+    auto kern = k_conv3x3_mfma<T, KS, OT, false>;
+    if constexpr (KS == 1) {
+        if (L.c_in == 3 && positions(in) >= 3) kern = k_conv3x3_mfma<T, KS, OT, true>;  // a window is 8 elements
+    }
+    launch(mk, kern, dim3(static_cast<unsigned>(grid)), dim3(kBlock), lds, st,
            static_cast<const T *>(x), in.n, in.h, in.w, L.c_in, L.stride, static_cast<const T *>(L.w), L.b,
-           L.c_out, L.act, static_cast<T *>(y), out.h, out.w);
+           L.c_out, L.act, static_cast<T *>(y), out.h, out.w, div28(out.h), div28(out.w));
 }
 
 // 16-bit storage: the matrix-core form when its weights fit 64 KB of LDS;
@@ -1278,7 +1282,7 @@ void launch_conv3x3(const void *x, dynconv_shape in, dynconv_shape out, const dy
                     hipStream_t st, Marks &mk) {
     const int ks = (9 * L.c_in + 31) / 32;
     if constexpr (sizeof(T) == 2) {
-        const size_t lds = static_cast<size_t>(L.c_out) * (ks * 32 + 8) * sizeof(T) + 4 * 32 * ks;
+        const size_t lds = static_cast<size_t>(L.c_out) * (ks * 32 + 8) * sizeof(T) + std::max(4 * 32 * ks, 384);
         if (lds <= kMaxDynLds) {
             const bool wide = L.c_out > 32;
 #define DC_C3(KS)                                                                         \

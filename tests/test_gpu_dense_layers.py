@@ -78,3 +78,18 @@ def test_conv3x3(dtype, stride, n, h, w, ci, o):
          "b": rng.normal(0, 0.1, o).astype(np.float32), "stride": stride, "act": 2}
     want = onet.conv3x3(x.transpose(0, 3, 1, 2).astype(np.float64), L["w"], L["b"], stride, 2)
     check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("n,h,w", [(1, 1, 2), (1, 2, 1), (1, 1, 3), (3, 1, 1), (5, 2, 2), (7, 9, 9), (2, 4, 8), (4, 5, 15),
+                                   (3, 3, 16), (6, 7, 17), (2, 1, 33), (2, 33, 1), (1, 64, 64)])
+def test_stem_tiles_across_rows_and_images(dtype, stride, n, h, w):
+    """Tiles of 16 positions that cross rows and images, windows that reach over
+    the borders and over the tensor's first and last elements."""
+    rng = inputs.rng_for(100 * h + w)
+    x = inputs.round_to_storage(rng.standard_normal((n, h, w, 3)), dtype)
+    L = {"kind": "conv3x3", "w": inputs.round_to_storage(rng.normal(0, 0.2, (40, 3, 3, 3)), dtype),
+         "b": rng.normal(0, 0.1, 40).astype(np.float32), "stride": stride, "act": 0}
+    want = onet.conv3x3(x.transpose(0, 3, 1, 2).astype(np.float64), L["w"], L["b"], stride, 0)
+    check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
