@@ -138,6 +138,23 @@ k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, co
             contract(acc, bx);
             finish(acc, pt * kPwPos + lane_p);
         }
+    } else if constexpr (sizeof(Frag) * KB > 128) {
+        // fp32 chunks of 256 channels: two of them in flight spill into fewer waves
+        // (64 x 7x7, 320 -> 1280 63.1 us, now 59.1; 64 x 14x14, 384 -> 96 25.0, now 22.6)
+        for (int64_t pt = slot * 8 + xcd; pt < ptiles; pt += step) {
+            const int64_t p = pt * kPwPos + lane_p;
+            floatx4 acc[OT];
+            init(acc);
+            for (int ch = 0; ch < nch; ++ch) {
+                Frag bx[KB];
+                load_x(bx, p, ch * KB * 32);
+                __syncthreads();  // every wave is done with the previous chunk
+                stage(ch * KB * 32);
+                __syncthreads();
+                contract(acc, bx);
+            }
+            finish(acc, p);
+        }
     } else {
         constexpr int WP = (ROWS * PIECES + kBlock - 1) / kBlock;
         Frag wv[WP], bn[KB];
@@ -190,8 +207,9 @@ k_conv1x1(const T *__restrict__ x, int64_t P, int C, const T *__restrict__ w, co
 // branches around the loads (what is in flight is known at every wait).
 // Accumulation as in k_conv1x1 (bias first, steps of 32 channels ascending), so
 // the outputs are the same.  Bound by the latency of the first loads; k_conv1x1
-// pays two barriers and a memory latency per 256 channels there.  At 7x7, one
-// image: 960 -> 320 12.1 -> 9.0 us, 320 -> 1280 7.8 -> 4.4, 576 -> 160 9.2 -> 6.1.
+// pays two barriers and a memory latency per 256 channels there.  One image, us
+// per launch in a graph, k_conv1x1 / this one: 7x7 960 -> 320 9.3 / 9.0, 320 -> 1280
+// 6.8 / 5.4, 56x56 144 -> 24 3.9 / 3.0; fp32 7x7 320 -> 1280 15.4 / 7.6.
 // The four waves of a workgroup take neighbouring output tiles of the same
 // positions.
 template <typename T, int D>
