@@ -1188,23 +1188,36 @@ void launch_conv1x1_ot(const void *x, int64_t P, int C, const void *w, const flo
     else if constexpr (kFits8) launch_conv1x1_k<T, OT, 8>(x, P, C, w, b, O, act, res, y, st, mk);
 }
 
-// One tile of 16 outputs x 16 positions per wave (k_conv1x1_tile) up to 1,024
-// tiles, a wave per SIMD (above, k_conv1x1's sharing of weights and x wins: 7x7,
-// batch 64, 576 -> 160, 1,960 tiles, 9.7 us against 12.4), or 2,048 with a single
-// step of contraction (56x56, one image, 24 -> 144, 1,764 tiles: 4.2 us against
-// 4.8; 112x112, 16 -> 96, 4,704 tiles: 6.1 against 4.9).
-bool use_conv1x1_tile(int64_t P, int C, int O) {
-    const int64_t tiles = ((P + 15) / 16) * ((O + 15) / 16);
-    return tiles <= (C <= 32 ? 2048 : 1024);
+// One tile of 16 outputs x 16 positions per wave (k_conv1x1_tile) while that
+// gives no compute unit more than four waves (one per SIMD): beyond, its loads
+// queue up and k_conv1x1's sharing of weights and x wins.  With one step of
+// contraction and rows of at most 96 bytes, up to 12.  Measured, us, k_conv1x1 /
+// this one (the unit's waves): fp16 28x28, one image, 576 -> 192 (4) 8.0 / 7.3,
+// 8 x 14x14, 576 -> 144 (8) 8.0 / 12.3, 64 -> 144 (8) 3.3 / 3.5, 56x56, 24 -> 144
+// (12) 3.3 / 3.1, 112x112, 64 -> 96 (28) 4.1 / 5.9; fp32 28x28, 576 -> 192 (4) 15.6 / 11.1,
+// 56x56, 32 -> 96 (8) 3.5 / 3.6, 24 -> 96 (8) 3.5 / 3.2.
+bool use_conv1x1_tile(size_t elem, int64_t P, int C, int O) {
+    const int nmt = (O + 15) / 16;
+    const int64_t groups = ((P + 15) / 16) * ((nmt + kWavesPerBlock - 1) / kWavesPerBlock);
+    const int64_t waves = (groups + 255) / 256 * std::min(nmt, kWavesPerBlock);
+    return waves <= (C <= 32 && C * elem <= 96 ? 12 : 4);
 }
-
 template <typename T>
 void launch_conv1x1(const void *x, int64_t P, int C, const void *w, const float *b, int O, int act,
                     const void *res, void *y, hipStream_t st, Marks &mk) {
-    if (use_conv1x1_tile(P, C, O)) {
-        constexpr int D = sizeof(T) == 2 ? 8 : 4;
+    if (use_conv1x1_tile(sizeof(T), P, C, O)) {
+        // where the contraction is short the ring is no longer than it: what was
+        // requested past the end would be waited for like the rest (28x28, one
+        // image, 64 -> 192, fp16 3.9 us with a ring of 8 steps for 2, now 3.1; fp32
+        // 32 -> 192 3.9, now 3.1)
+        const int nks = (C + 31) / 32;
+        constexpr int kRing = sizeof(T) == 2 ? 8 : 4;
+        auto kern = k_conv1x1_tile<T, kRing>;
+        if (nks == 1) kern = k_conv1x1_tile<T, 2>;
+        else if (nks == 2) kern = k_conv1x1_tile<T, 3>;
+        else if (nks <= 4 && kRing > 4) kern = k_conv1x1_tile<T, 5>;
         const int nog = ((O + 15) / 16 + kWavesPerBlock - 1) / kWavesPerBlock;
-        launch(mk, k_conv1x1_tile<T, D>, dim3(static_cast<unsigned>((P + 15) / 16 * nog)), dim3(kBlock), 0, st,
+        launch(mk, kern, dim3(static_cast<unsigned>((P + 15) / 16 * nog)), dim3(kBlock), 0, st,
                static_cast<const T *>(x), static_cast<int>(P), C, static_cast<const T *>(w), b, O, act,
                static_cast<const T *>(res), static_cast<T *>(y), nog);
         return;

@@ -93,3 +93,28 @@ def test_stem_tiles_across_rows_and_images(dtype, stride, n, h, w):
          "b": rng.normal(0, 0.1, 40).astype(np.float32), "stride": stride, "act": 0}
     want = onet.conv3x3(x.transpose(0, 3, 1, 2).astype(np.float64), L["w"], L["b"], stride, 0)
     check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("c", [8, 24, 32, 40, 64, 72, 96, 104, 128, 136, 224, 256, 264, 288, 512, 520])
+def test_conv1x1_tile_rings(dtype, c):
+    """One to seventeen contraction steps: rings as short as the contraction, the
+    longest ring's full rounds and remainders; a partial last tile of outputs."""
+    rng = inputs.rng_for(c)
+    x = inputs.round_to_storage(rng.standard_normal((1, 5, 7, c)), dtype)
+    L = {"kind": "conv1x1", "w": inputs.round_to_storage(rng.normal(0, 0.05, (88, c)), dtype),
+         "b": rng.normal(0, 0.1, 88).astype(np.float32), "act": 0}
+    want = x.reshape(-1, c).astype(np.float64) @ L["w"].astype(np.float64).T + L["b"]
+    check(run(x, [L], dtype), want.reshape(1, 5, 7, 88), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("n,c,o", [(1024, 24, 64), (1025, 24, 64), (3072, 24, 64), (3073, 24, 64), (4096, 40, 64),
+                                   (4097, 40, 64), (4096, 32, 72), (4096, 16, 16), (16 * 1024, 16, 16)])
+def test_conv1x1_on_both_sides_of_the_tile_kernel(dtype, n, c, o):
+    rng = inputs.rng_for(n + c)
+    x = inputs.round_to_storage(rng.standard_normal((n, 1, 1, c)), dtype)
+    L = {"kind": "conv1x1", "w": inputs.round_to_storage(rng.normal(0, 0.05, (o, c)), dtype),
+         "b": rng.normal(0, 0.1, o).astype(np.float32), "act": 2}
+    want = np.clip(x.reshape(-1, c).astype(np.float64) @ L["w"].astype(np.float64).T + L["b"], 0.0, 6.0)
+    check(run(x, [L], dtype), want.reshape(n, 1, 1, o), dtype)
