@@ -282,13 +282,14 @@ k_conv1x1_tile(const T *__restrict__ x, int P, int C, const T *__restrict__ w, c
 // uses it, so a lane issues (S (R - 1) + 3) x 3 tap loads for R outputs
 // instead of 9 R.  The 72 weights of the lane's 8 channels are contiguous in
 // memory ([C][9]): each lane reads them itself, with the taps of the first
-// rows in flight behind them.  Each output accumulates in fp32 from the bias,
+// rows in flight behind them, or (LDSW, few channels) the workgroup stages all
+// of them in LDS first.  Each output accumulates in fp32 from the bias,
 // taps in (kh, kw) order; rows outside the image are skipped.
 // Bound by the latency of these loads: few work items take small R, so that
-// more waves are in flight (launch_dwconv_s).  All weights staged per
-// workgroup through LDS (9 C two-byte loads and a division each, and a barrier)
-// took 8.2 us for 14x14x576 -> 7x7 of one image, now 4.1; at batch 64 9.6, now
-// 7.0.
+// more waves are in flight (launch_dwconv_s).  Staging 9 C weights per
+// workgroup (two-byte loads, a division each, and a barrier) took 8.2 us for
+// 14x14x576 -> 7x7 of one image, lanes reading their own 4.1; at 64 x 112x112x32,
+// where it is one weight per lane, LDS is the faster (launch_dwconv_r).
 template <typename T>
 struct DwWeights {  // [8][9]
     struct __attribute__((packed, aligned(2))) raw_t {
@@ -312,12 +313,32 @@ struct DwWeights<float> {
     __device__ __forceinline__ float at(int u, int k) const { return w[u * 9 + k]; }
 };
 
-template <typename T, int S, int R>
+// The weights of 8 channels out of LDS, transposed [9][C].
+template <typename T>
+struct DwWeightsLds {
+    typename io<T>::vec8 w[9];
+    __device__ __forceinline__ void load(const T *p, int C) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) w[k] = io<T>::raw8(p + k * C);
+    }
+    __device__ __forceinline__ float at(int u, int k) const { return static_cast<float>(w[k][u]); }
+};
+
+template <typename T, int S, int R, bool LDSW>
 __global__ void __launch_bounds__(kBlock)
 k_dwconv3x3(const T *__restrict__ x, int N, int H, int W, int C, const T *__restrict__ w,
             const float *__restrict__ b, int act, T *__restrict__ y, int Ho, int Wo) {
     typedef typename io<T>::vec8 V;
     constexpr int ROWS = S * (R - 1) + 3;  // input rows of R output rows
+    extern __shared__ __align__(16) unsigned char dw_smem[];
+    T *wt = reinterpret_cast<T *>(dw_smem);  // LDSW: [9][C]
+    if constexpr (LDSW) {
+        for (int i = threadIdx.x; i < 9 * C; i += kBlock) {
+            const int ch = i / 9, k = i % 9;
+            wt[k * C + ch] = w[i];
+        }
+        __syncthreads();
+    }
     const float lo = act_lo(act), hi = act_hi(act);
     const uint32_t cgs = C / 8;
     const uint32_t tasks = Wo * cgs;
@@ -331,8 +352,9 @@ k_dwconv3x3(const T *__restrict__ x, int N, int H, int W, int C, const T *__rest
         const uint32_t task = chunk * kBlock + threadIdx.x;
         if (task >= tasks) continue;
         const int j = task / cgs, c = (task - j * cgs) * 8;
-        DwWeights<T> wk;
-        wk.load(w + c * 9);
+        std::conditional_t<LDSW, DwWeightsLds<T>, DwWeights<T>> wk;
+        if constexpr (LDSW) wk.load(wt + c, C);
+        else wk.load(w + c * 9);
         float acc[R][8];
 #pragma unroll
         for (int q = 0; q < R; ++q)

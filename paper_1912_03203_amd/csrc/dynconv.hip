@@ -1237,9 +1237,12 @@ void launch_conv1x1(const void *x, int64_t P, int C, const void *w, const float 
 }
 
 // Output rows per depthwise task: 4 (16-bit) or 2 where that still gives
-// kDwMinItems workgroups, else fewer: 9 R / (S (R - 1) + 3) fewer tap loads
-// against waves in flight.
-constexpr int64_t kDwMinItems = 1024;
+// kDwMinWaves waves, a wave per SIMD, else fewer: 9 R / (S (R - 1) + 3) fewer tap
+// loads against waves in flight.  Measured with the projection behind it, fewer
+// rows / more, us: fp32, stride 2, 16 x 56x56x144 (2 rows: 1,792 waves) 16.6 / 13.9,
+// 8 x 14x14x576 (256 waves) 10.7 / 11.5; fp16, 64 x 7x7x960 (4 rows: 2,048) 13.6 / 12.2,
+// 2 x 56x56x144 (448) 7.3 / 7.9.
+constexpr int64_t kDwMinWaves = 1024;
 
 template <typename T, int S, int R>
 void launch_dwconv_r(const void *x, dynconv_shape in, dynconv_shape out, int C, const void *w, const float *b,
@@ -1248,18 +1251,26 @@ void launch_dwconv_r(const void *x, dynconv_shape in, dynconv_shape out, int C, 
     int64_t items = static_cast<int64_t>(out.n) * ((out.h + R - 1) / R) * chunks;
     if (items > 4096) items = 4096;
     if (items < 1) items = 1;
-    launch(mk, k_dwconv3x3<T, S, R>, dim3(static_cast<unsigned>(items)), dim3(kBlock), 0, st,
-           static_cast<const T *>(x), in.n, in.h, in.w, C, static_cast<const T *>(w), b, act, static_cast<T *>(y),
-           out.h, out.w);
+    auto go = [&](auto kern, size_t lds) {
+        launch(mk, kern, dim3(static_cast<unsigned>(items)), dim3(kBlock), lds, st, static_cast<const T *>(x), in.n,
+               in.h, in.w, C, static_cast<const T *>(w), b, act, static_cast<T *>(y), out.h, out.w);
+    };
+    // Weights through LDS, staged per workgroup, where that is at most 4 of them
+    // per working lane (fp32 at stride 1: 8): per lane / through LDS, us, 64 x
+    // 112x112x32 (1.1 per lane) fp16 39.2 / 36.9, fp32 89.2 / 77.4, 64 x 56x56x144 (5.1)
+    // fp32 103 / 95, stride 2 42 / 45; 512 x 7x7x64 (10) fp16 8.4 / 8.8
+    const int64_t lanes = std::min<int64_t>(kBlock, static_cast<int64_t>(out.w) * (C / 8));
+    if (9 * C <= lanes * (sizeof(T) == 4 && S == 1 ? 8 : 4)) go(k_dwconv3x3<T, S, R, true>, 9 * C * sizeof(T));
+    else go(k_dwconv3x3<T, S, R, false>, 0);
 }
 
 template <typename T, int S>
 void launch_dwconv_s(const void *x, dynconv_shape in, dynconv_shape out, int C, const void *w, const float *b,
                      int act, void *y, hipStream_t st, Marks &mk) {
-    const int64_t per_row = out.n * ((static_cast<int64_t>(out.w) * (C / 8) + kBlock - 1) / kBlock);
-    if (sizeof(T) == 2 && per_row * ((out.h + 3) / 4) >= kDwMinItems)
+    const int64_t per_row = out.n * ((static_cast<int64_t>(out.w) * (C / 8) + kWave - 1) / kWave);
+    if (sizeof(T) == 2 && per_row * ((out.h + 3) / 4) >= kDwMinWaves)
         launch_dwconv_r<T, S, sizeof(T) == 2 ? 4 : 2>(x, in, out, C, w, b, act, y, st, mk);
-    else if (per_row * ((out.h + 1) / 2) >= kDwMinItems)
+    else if (per_row * ((out.h + 1) / 2) >= kDwMinWaves)
         launch_dwconv_r<T, S, 2>(x, in, out, C, w, b, act, y, st, mk);
     else
         launch_dwconv_r<T, S, 1>(x, in, out, C, w, b, act, y, st, mk);

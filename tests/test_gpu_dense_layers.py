@@ -118,3 +118,18 @@ def test_conv1x1_on_both_sides_of_the_tile_kernel(dtype, n, c, o):
          "b": rng.normal(0, 0.1, o).astype(np.float32), "act": 2}
     want = np.clip(x.reshape(-1, c).astype(np.float64) @ L["w"].astype(np.float64).T + L["b"], 0.0, 6.0)
     check(run(x, [L], dtype), want.reshape(n, 1, 1, o), dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("n,h,w,c", [(1, 3, 64, 8), (2, 9, 41, 32), (40, 21, 40, 40), (9, 30, 88, 96), (3, 5, 60, 144),
+                                     (30, 27, 70, 32)])
+def test_depthwise_weights_through_lds(dtype, stride, n, h, w, c):
+    """Few weights per working lane: staged per workgroup, 1, 2 and 4 rows per task."""
+    rng = inputs.rng_for(n * h + c)
+    x = inputs.round_to_storage(rng.standard_normal((n, h, w, c)), dtype)
+    L = {"kind": "block", "stride": stride, "acts": (2, 1, 0), "w1": None, "b1": None,
+         "w2": inputs.round_to_storage(rng.normal(0, 0.3, (c, 9)), dtype), "b2": rng.normal(0, 0.1, c).astype(np.float32),
+         "w3": inputs.round_to_storage(rng.normal(0, 0.2, (16, c)), dtype), "b3": rng.normal(0, 0.1, 16).astype(np.float32)}
+    want = onet.dense_block(x.transpose(0, 3, 1, 2).astype(np.float64), L)
+    check(run(x, [L], dtype), want.transpose(0, 2, 3, 1), dtype)
