@@ -521,9 +521,13 @@ k_expand_dw(const T *__restrict__ x, int N, int H, int W, int C, const T *__rest
         origin(it, n, i0, j0);
         const int hb = S * i0 - 1, wb = S * j0 - 1;
         // the item's B fragments (region x) and activation bounds, kept for
-        // every slice (a select per value and slice instead: 49.3 us for 64 x
-        // 112x112x16 -> 56x56x96, now 47.2); waves past the last tile repeat it (same values), so
-        // every wave issues the same MFMAs
+        // every slice (kBounds; a select per value and slice instead: 49.3 us for
+        // 64 x 112x112x16 -> 56x56x96, now 47.2, but with stride 1 and one
+        // contraction step the bounds' registers cost more: 64 x 56x56x24, hidden 144,
+        // with its projection 62.1 us by selects, 66.4 so); waves past the last tile
+        // repeat it (same values), so every wave issues the same MFMAs
+        constexpr bool kBounds = S == 2 || KS == 2;
+        uint32_t inside = 0;
         Frag bx[TPW][KS];
         float lo_t[TPW], hi_t[TPW];
 #pragma unroll
@@ -540,6 +544,7 @@ k_expand_dw(const T *__restrict__ x, int N, int H, int W, int C, const T *__rest
             const bool in = slot < RP && hh >= 0 && hh < H && ww >= 0 && ww < W;
             lo_t[jt] = in ? lo1 : 0.0f;
             hi_t[jt] = in ? hi1 : 0.0f;
+            inside |= static_cast<uint32_t>(in) << jt;
         }
         for (int sl = 0; sl < nsl; ++sl) {
             const int e0 = sl * 32;
@@ -573,7 +578,10 @@ k_expand_dw(const T *__restrict__ x, int N, int H, int W, int C, const T *__rest
                     if (t < NT) {
                         float o[4];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) o[v] = clamp_act(d[v], lo_t[jt], hi_t[jt]);
+                        for (int v = 0; v < 4; ++v)
+                            o[v] = kBounds                 ? clamp_act(d[v], lo_t[jt], hi_t[jt])
+                                   : (inside >> jt) & 1u ? clamp_act(d[v], lo1, hi1)
+                                                           : 0.0f;
                         io<T>::store4(h1 + slot * HP + m * 16 + 4 * g, o);
                     }
                 }
