@@ -692,14 +692,21 @@ int32_t *band_counts_of(const char *base, const StackLayout &L, int32_t b) {
     return at<int32_t>(base, L.bands + per * static_cast<size_t>(L.nbands) * b);
 }
 
+template <typename P>
+void launch_band_counts_of(const char *base, const StackLayout &L, int nbands, int32_t n_blocks, int32_t *counts,
+                           hipStream_t st, Marks &mk) {
+    auto go = [&](auto kern, int threads) {
+        launch(mk, kern, dim3(n_blocks), dim3(threads), 0, st, at<const P>(base, L.bands), nbands, counts);
+    };
+    if (nbands <= 8 * 64) go(k_band_counts<P, 64>, 64);
+    else if (nbands <= 8 * 256) go(k_band_counts<P, 256>, 256);
+    else go(k_band_counts<P, 1024>, 1024);
+}
+
 void launch_band_counts(const char *base, const StackLayout &L, int32_t n_blocks, int32_t *counts, hipStream_t st,
                         Marks &mk) {
-    if (L.geom.R != 0)
-        launch(mk, k_band_counts<uint16_t>, dim3(n_blocks), dim3(kCountThreads), 0, st,
-               at<const uint16_t>(base, L.bands), L.nbands, counts);
-    else
-        launch(mk, k_band_counts<int2>, dim3(n_blocks), dim3(kCountThreads), 0, st, at<const int2>(base, L.bands),
-               L.nbands, counts);
+    if (L.geom.R != 0) launch_band_counts_of<uint16_t>(base, L, L.nbands, n_blocks, counts, st, mk);
+    else launch_band_counts_of<int2>(base, L, L.nbands, n_blocks, counts, st, mk);
 }
 
 void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks,
@@ -743,8 +750,7 @@ void stack_walk(const void *x, void *y, dynconv_shape s, dynconv_dtype dt, const
             src = dst;
         }
         if (!dense && (counts || (!plan.exec && plan.list_counts)) && plan.note("k_band_counts"))
-            launch(mk, k_band_counts<int2>, dim3(n_blocks), dim3(kCountThreads), 0, st, at<const int2>(base, L.bands),
-                   static_cast<int>(ncells), cnt_all);
+            launch_band_counts_of<int2>(base, L, static_cast<int>(ncells), n_blocks, cnt_all, st, mk);
         return;
     }
     if (L.fused) {

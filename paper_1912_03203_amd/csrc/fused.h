@@ -643,14 +643,13 @@ k_block_fused(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int
 
 // counts[2b], counts[2b+1] = sums of the per-patch (per-cell) counts of block b:
 // int2 pairs, or both counts in the bytes of a uint16 (k_block_wide).  One
-// workgroup per block; every thread has 8 loads in flight, because the time is
-// the loads' latency (6,272 cells of a 32 x 56x56 block: 7.0 us with 256 threads
-// and one load at a time, 2.9 so).
-constexpr int kCountThreads = 1024;
-template <typename P>
-__global__ void __launch_bounds__(kCountThreads)
+// workgroup of NT threads per block; every thread has 8 loads in flight, because
+// the time is the loads' latency (6,272 cells of a 32 x 56x56 block: 7.0 us with
+// 256 threads and one load at a time, 2.9 with 1,024 so).  Few counts take one
+// wave, which has nothing to exchange (36 cells 2.2 us with 1,024 threads, 1.9 so).
+template <typename P, int NT>
+__global__ void __launch_bounds__(NT)
 k_band_counts(const P *__restrict__ band_counts, int nbands, int32_t *__restrict__ counts) {
-    __shared__ int2 part[kCountThreads / kWave];
     const int b = blockIdx.x, tid = threadIdx.x;
     const P *src = band_counts + static_cast<int64_t>(b) * nbands;
     int a = 0, d = 0;
@@ -664,16 +663,16 @@ k_band_counts(const P *__restrict__ band_counts, int nbands, int32_t *__restrict
         }
     };
     int i = tid;
-    for (; i + 7 * kCountThreads < nbands; i += 8 * kCountThreads) {
+    for (; i + 7 * NT < nbands; i += 8 * NT) {
         P v[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = src[i + q * kCountThreads];
+        for (int q = 0; q < 8; ++q) v[q] = src[i + q * NT];
 #pragma unroll
         for (int q = 0; q < 8; ++q) add(v[q]);
     }
     P v[7];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = (i + q * kCountThreads < nbands) ? src[i + q * kCountThreads] : P{};
+    for (int q = 0; q < 7; ++q) v[q] = (i + q * NT < nbands) ? src[i + q * NT] : P{};
 #pragma unroll
     for (int q = 0; q < 7; ++q) add(v[q]);
 #pragma unroll
@@ -681,14 +680,19 @@ k_band_counts(const P *__restrict__ band_counts, int nbands, int32_t *__restrict
         a += __shfl_down(a, off);
         d += __shfl_down(d, off);
     }
-    if (tid % kWave == 0) part[tid / kWave] = make_int2(a, d);
-    __syncthreads();
-    if (tid == 0) {
+    if constexpr (NT > kWave) {
+        __shared__ int2 part[NT / kWave];
+        if (tid % kWave == 0) part[tid / kWave] = make_int2(a, d);
+        __syncthreads();
+        if (tid == 0) {
 #pragma unroll
-        for (int w = 1; w < kCountThreads / kWave; ++w) {
-            a += part[w].x;
-            d += part[w].y;
+            for (int w = 1; w < NT / kWave; ++w) {
+                a += part[w].x;
+                d += part[w].y;
+            }
         }
+    }
+    if (tid == 0) {
         counts[2 * b] = a;
         counts[2 * b + 1] = d;
     }
