@@ -120,9 +120,8 @@ void launch(Marks &mk, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t l
 // 2^32 threads, and past that a launch leaves the rest out without an error.
 // Whole groups of 8 along x (one per XCD).
 dim3 grid_xy(int64_t blocks) {
-    constexpr int64_t kAlong = int64_t{1} << 22;  // 2^31 threads in workgroups of 512
-    return blocks <= kAlong ? dim3(static_cast<unsigned>(blocks))
-                            : dim3(kAlong, static_cast<unsigned>((blocks + kAlong - 1) / kAlong));
+    return blocks <= kGridAlong ? dim3(static_cast<unsigned>(blocks))
+                                : dim3(kGridAlong, static_cast<unsigned>((blocks + kGridAlong - 1) / kGridAlong));
 }
 
 // ------------------------------------------------------------ workspaces

@@ -184,10 +184,11 @@ template <> struct mma<float> {
     }
 };
 
-// The workgroup's number in a grid that grid_xy (dynconv.hip) cut.
-__device__ __forceinline__ int64_t block_xy() {
-    return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-}
+// The workgroup's number in a grid that grid_xy (dynconv.hip) cut: rows of
+// kGridAlong workgroups.  (The grid's own width would be one more load before
+// the first address.)
+constexpr int kGridAlong = 1 << 22;  // 2^31 threads in workgroups of 512
+__device__ __forceinline__ int block_xy() { return static_cast<int>(blockIdx.y * kGridAlong + blockIdx.x); }
 
 // Activation as one clamp: kind 0 none, 1 ReLU, 2 ReLU6.  act_lo / act_hi
 // are uniform, so activate() is a single branch-free v_med3.
@@ -268,7 +269,7 @@ k_rowcount(const uint8_t *__restrict__ mask, int N, int H, int W, int r, int2 *_
            uint64_t *__restrict__ words) {
     __shared__ uint64_t rows[kWavesPerBlock][7][kMaxSeg];  // rows h-r .. h+r, r <= 3
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int64_t row = block_xy() * kWavesPerBlock + wave;
+    const int64_t row = static_cast<int64_t>(block_xy()) * kWavesPerBlock + wave;
     if (row >= static_cast<int64_t>(N) * H) return;  // uniform per wave; no block barrier below
     const int n = static_cast<int>(row / H), h = static_cast<int>(row % H);
     const int nseg = (W + kWave - 1) / kWave;
@@ -359,7 +360,7 @@ k_compact(const uint64_t *__restrict__ words, int N, int H, int W, int r,
     __shared__ int2 part[kWavesPerBlock];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int64_t nrows = static_cast<int64_t>(N) * H;
-    const int64_t row = block_xy() * kWavesPerBlock + wave;
+    const int64_t row = static_cast<int64_t>(block_xy()) * kWavesPerBlock + wave;
     int2 base = make_int2(0, 0);  // (active, dilated) positions before the row
     int dil_off[3];               // dilated positions before rows h-1, h, h+1
     if constexpr (SCAN) {

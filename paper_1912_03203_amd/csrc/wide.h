@@ -248,7 +248,7 @@ k_block_wide(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int 
     // XCD-aware: workgroup i runs on XCD i % 8, so consecutive patches
     // (which share ring rows and columns) go to the same XCD.
     const int per_xcd = (npatch + 7) / 8;
-    const int bid = static_cast<int>(block_xy());
+    const int bid = block_xy();
     const int patch = (bid % 8) * per_xcd + bid / 8;
     if (bid / 8 >= per_xcd || patch >= npatch) return;  // uniform per workgroup
     const int pimg = G.nph * G.npw;
