@@ -263,9 +263,12 @@ dynconv_status dynconv_stack_forward(const void *x, void *y, dynconv_shape s, dy
 
 /*
  * Launch sequence of dynconv_stack_forward, for profiling: stores up to `cap`
- * kernel names (static strings) in launch order into `names` (may be NULL
- * when cap is 0) and returns the number of launches, or -1 for invalid
- * arguments.  in_place says whether the call will have y == x.  The count
+ * names (static strings) in launch order into `names` (may be NULL when cap is
+ * 0) and returns the number of launches, or -1 for invalid arguments.  A name
+ * stands for a step and every kernel that runs it: "k_block_fused" is a block in
+ * one launch on a patch kernel (a tracer shows k_block_fused or k_block_wide),
+ * "k_conv1x1" and "k_conv3x3" of a network include k_conv1x1_tile and
+ * k_conv3x3_mfma.  in_place says whether the call will have y == x.  The count
  * reduction (k_band_counts, last) is listed as if counts were requested; a
  * call without counts skips it and leaves its event pair unused.
  */

@@ -36,12 +36,17 @@
 // share of the grid (copy and next mask unit, one position per lane), so
 // the copies overlap the active work of the other waves.  A dense region of
 // the mask is spread over many CUs, and the span follows the active work.
-// Bound by vector issue: a cell's slice issues about 150 vector instructions,
-// 72 of them the depthwise's multiply-adds (192 before the two-row lanes in
-// dense launches, and 120 conversions more in bf16).  Measured per block: dense
-// 200 x 64x64x32 bf16 177 -> 139 us; gated at 0.25, 768 x 64x64x32 bf16 412 -> 385
-// us, 32 x 64x64x32 fp16 15.7 -> 15.3; one 32 x 56x56x24 block with its counts
-// 18.3 -> 17.2.
+// What bounds it, by the counters (share of a launch's cycles with the LDS active
+// / with vector instructions issuing): fp16 dense the LDS, 73 % / 62 % at 32 images
+// of 64x64x32, 88 % / 71 % at 200, 31 % of the LDS cycles bank conflicts; bf16, which
+// widens taps and weights before their multiply-adds, vector issue, 82 % / 98 %
+// dense at 200 images, 58 % / 81 % gated at 768; fp16 gated at 32 images neither
+// (52 % / 57 %) but the chains of the two or three cells of a SIMD.  The two-row
+// lanes took a dense fp16 launch from 234 vector instructions per cell and slice,
+// everything included, to 188 and left its time (25.2, 25.4 us at 32 images): they
+// pay in bf16.  Measured per block: dense 200 x 64x64x32 bf16 177 -> 139 us; gated at
+// 0.25, 768 x 64x64x32 bf16 412 -> 385 us, 32 x 64x64x32 fp16 19.9 -> 19.5; gated fp16 at
+// 0.1 they cost 2 to 3 % (1 x 64x64x32, 8 blocks 77.6 -> 80.3, 32 images 95.5 -> 97.7).
 // The arithmetic of every output element is the one of the kernel chain
 // (k_expand, k_dw_project): the same operand fragments, summation order and
 // roundings.  Input and output must be different buffers (a cell's ring is

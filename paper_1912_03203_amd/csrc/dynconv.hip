@@ -525,10 +525,11 @@ constexpr int32_t kStackFlags = kStackDense | kStackUnfused | kStackGSoftmax;
 int mask_mode_of(int32_t flags) { return (flags & kStackGSoftmax) ? 1 : 0; }
 
 // The one-launch block kernels cover up to 64 channels in fp32, and in
-// fp16/bf16 up to 128 and the whole 32-channel steps up to 192 (160 and 192,
-// where a cut of the map exists; MobileNetV2's 7x7x160 pair at batch 64: 151 us
-// on the kernel chain, 48 on one launch per block); wider blocks run the unfused
-// kernel chain.
+// fp16/bf16 up to 128 and, where pick_wide_160 finds it the faster, 160 and 192
+// (MobileNetV2's 7x7x160 pair at batch 64: 151 us on the kernel chain, 48 on one
+// launch per block).  Wider blocks run the unfused kernel chain, and so do the
+// widths between 128 and 192 that are no whole steps of 32 channels: the kernel
+// would hold them, but no network here has them, and they are not measured.
 bool use_fused(dynconv_shape s, dynconv_dtype dt, int32_t flags) {
     if (flags & kStackUnfused) return false;
     if (dt == DYNCONV_F32) return s.c <= kMaxFusedC;

@@ -182,7 +182,7 @@ __device__ __forceinline__ typename mma<T>::frag ldf_at(const T *base, uint32_t 
 // The mask unit (Eq. 2, Eq. 8 at zero noise) on a row staged in LDS: the fp32
 // multiply-add chain of k_mask, channels ascending from +0, then the bias,
 // strict threshold.  32 channels at a time: their loads overlap.
-template <typename T, int KS>
+template <typename T>
 __device__ __forceinline__ bool mask_of_row(const T *row, int C, const float *wm, float bm, int mode) {
     typedef const __attribute__((address_space(4))) float *cfptr;
     cfptr w = (cfptr)(wm);
@@ -398,7 +398,7 @@ k_block_wide(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int 
     if (!DENSE && wm_self) {
         lds_barrier();  // the region's x, for the block's own mask unit
         if (s_img) {
-            bit = mask_of_row<T, KS>(xs + tid * XP, C, wm_self, bm_self, mask_mode);
+            bit = mask_of_row<T>(xs + tid * XP, C, wm_self, bm_self, mask_mode);
             if (mask_self && s_own) (mask_self + pos0)[static_cast<uint32_t>(srow * W + scol)] = bit ? 1 : 0;
         }
     }
@@ -643,7 +643,7 @@ k_block_wide(const T *__restrict__ xin, T *__restrict__ yout, int N, int H, int 
     // ---- the next block's mask unit on the stored values
     if (!SHUF && mask_next && s_own)
         (mask_next + pos0)[static_cast<uint32_t>(srow * W + scol)] =
-            mask_of_row<T, KS>(xs + tid * XP, C, wm_next, bm_next, mask_mode) ? 1 : 0;
+            mask_of_row<T>(xs + tid * XP, C, wm_next, bm_next, mask_mode) ? 1 : 0;
 }
 
 }  // namespace dynconv
