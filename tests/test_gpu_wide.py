@@ -1,7 +1,9 @@
 """The channel-parallel one-launch block kernel against the kernel chain, byte
 for byte, where its tiling changes: chunks of 64 or 128 hidden channels (one,
-several, a partial last one), 2, 4 or 8 tiles of needed positions, contraction
-tails, single rows, columns and positions, empty and full masks."""
+several, a partial last one), 2, 4 or 8 tiles of needed positions (above 128
+channels 2 or 4, and maps without such a cut), contraction tails, single rows,
+columns and positions, empty, full and nearly full masks, more patches than one
+grid dimension holds."""
 import numpy as np
 import pytest
 import torch
@@ -34,7 +36,9 @@ CASES = [
     ("f16", (1, 3, 1000, 112, 144), 0.3, 1),     # 97-128 channels, 8 needed tiles
     ("f16", (5, 7, 7, 160, 960), 0.4, 2),        # 2 needed tiles
     ("bf16", (2, 16, 15, 160, 304), 0.4, 2),     # 4 needed tiles, chunks of 64
-    ("f16", (1, 9, 1, 192, 80), 0.5, 1),
+    ("f16", (1, 9, 1, 192, 80), 0.5, 1),         # less scratch on the chain
+    ("f16", (1, 9, 1, 192, 208), 0.5, 1),        # one column, several chunks of 64
+    ("bf16", (5, 14, 9, 192, 192), 0.4, 2),
     ("f16", (1, 100, 100, 160, 160), 0.9, 1),    # 4 needed tiles, all of them full
     ("bf16", (1, 60, 60, 192, 176), 0.9, 1),
     ("f16", (1, 112, 112, 160, 160), 0.9, 2),    # 160 and 192 channels without a cut: the chain
