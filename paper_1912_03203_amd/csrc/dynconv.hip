@@ -550,13 +550,14 @@ bool use_cells(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int
 // Which patch kernel a stack of up to 128 channels takes: the channel-parallel
 // one (its patches), or k_block_fused (R = 0); wide_most_patches has the line.
 WideGeom pick_wide(dynconv_shape s, dynconv_dtype dt, const dynconv_block *blks, int32_t n_blocks, bool dense,
-                   int64_t max_patches) {
-    const WideGeom g = wide_geom(s, max_patches);
+                   int64_t fused_patches) {
+    // at most four of its patches share a patch of k_block_fused's room for counts
+    const WideGeom g = wide_geom(s, 4 * fused_patches);
     if (g.R == 0 || s.c > fused_max_c(dt)) return g;
     WideWork w{};
     for (int32_t b = 0; b < n_blocks; ++b) w.add(blks[b].c_hidden);
     const int64_t patches = static_cast<int64_t>(s.n) * g.nph * g.npw;
-    return patches <= wide_most_patches(s.c, w, dense) ? g : WideGeom{};
+    return patches <= wide_most_patches(s.c, w, dense, fused_patches) ? g : WideGeom{};
 }
 
 // 160 and 192 channels: the channel-parallel kernel, or the kernel chain (R = 0),
@@ -604,7 +605,7 @@ StackLayout stack_layout(dynconv_shape s, const dynconv_block *blks, int32_t n_b
             // per-patch counts: 8 bytes a patch of k_block_fused; the
             // channel-parallel kernel packs 2 bytes into the same room
             L.nbands = fused_patch_count(s, dt);
-            L.geom = pick_wide(s, dt, blks, n_blocks, (flags & kStackDense) != 0, int64_t{4} * L.nbands);
+            L.geom = pick_wide(s, dt, blks, n_blocks, (flags & kStackDense) != 0, L.nbands);
         } else {
             L.geom = pick_wide_160(s, blks, n_blocks, (flags & kStackDense) != 0);
         }

@@ -165,14 +165,19 @@ struct WideWork {
 //     16 / 20
 //   up to 32 channels, fp32: 1 x 32x32x32 (128 patches) 17.1 / 11.2, 16 x 48x48x32
 //     (576) 30 / 39
+// A map that k_block_fused cuts into more than 512 patches costs it a second
+// round, which moves the line to twice as many, and to 1,024 at most: bf16
+// 80 x 26x26 (960 patches, 560 of k_block_fused) at 0.5 active and dense: 64
+// channels, hidden 384 65 / 52 and 65 / 55, hidden 256 49 / 42 and 48 / 43; 40
+// channels, hidden 240 47 / 40 and 47 / 42, hidden 160 (line 512) 35 / 39 and 34 / 39.
 // Wider blocks have no other one-launch kernel (64 x 14x14x96 42 / 17.5, when
 // k_block_fused took up to 128 channels; fp32 16 x 48x48x64 144 / 91).
-inline int64_t wide_most_patches(int c, const WideWork &w, bool dense) {
+inline int64_t wide_most_patches(int c, const WideWork &w, bool dense, int64_t fused_patches) {
     if (c <= 32) return 256;
     if (w.most <= 128) return INT64_MAX;
     const double fill = static_cast<double>(w.hidden) / static_cast<double>(std::max<int64_t>(w.chunks, 1) * 128);
-    if (fill > 0.9) return dense && w.hidden < 384 * w.blocks ? 512 : 768;
-    return fill > 0.7 ? 512 : 256;
+    const int64_t most = fill > 0.9 ? (dense && w.hidden < 384 * w.blocks ? 512 : 768) : fill > 0.7 ? 512 : 256;
+    return fused_patches > 512 ? std::min<int64_t>(2 * most, 1024) : most;
 }
 
 }  // namespace dynconv

@@ -56,10 +56,10 @@ static void check(dynconv_shape s, int elem) {
     REQUIRE(exact(g.slots * pieces + 4 * per, pieces, div20_mul(pieces)));
 }
 
-static int64_t most(int c, int e, bool dense, int blocks = 1) {
+static int64_t most(int c, int e, bool dense, int blocks = 1, int64_t fused_patches = 512) {
     WideWork w{};
     for (int b = 0; b < blocks; ++b) w.add(e);
-    return wide_most_patches(c, w, dense);
+    return wide_most_patches(c, w, dense, fused_patches);
 }
 
 // both sides of the measured lines against k_block_fused
@@ -70,7 +70,11 @@ static bool lines() {
     return most(64, 64, true) == INT64_MAX && most(40, 128, false) == INT64_MAX && most(64, 384, true, 3) == 768 &&
            most(64, 384, false) == 768 && most(64, 256, true, 2) == 512 && most(64, 256, false) == 768 &&
            most(48, 288, true) == 512 && most(48, 192, false) == 512 && most(40, 160, false) == 256 &&
-           most(32, 384, true) == 256 && wide_most_patches(64, mixed, true) == 512;
+           most(32, 384, true) == 256 && wide_most_patches(64, mixed, true, 512) == 512 &&
+           // a second round of k_block_fused
+           most(64, 384, true, 2, 513) == 1024 && most(64, 256, true, 1, 560) == 1024 &&
+           most(48, 288, false, 1, 560) == 1024 && most(40, 160, false, 1, 560) == 512 &&
+           most(40, 128, false, 1, 560) == INT64_MAX && most(32, 384, true, 1, 560) == 256;
 }
 
 int main() {
